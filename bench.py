@@ -38,7 +38,8 @@ METRIC = "MLUPS + % HBM roofline, D3Q27 512^3 FP32 step; adjoint/forward time ra
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E
 BYTES_PER_NODE = 27 * 4 * 2 + 3 * 4
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_step_d3q27_f32_512_counters.json")
-KERNEL_SOURCES = ["paper_1202_6081_amd/csrc/kernels.hip", "paper_1202_6081_amd/csrc/collide_d3q27.hpp",
+KERNEL_SOURCES = ["paper_1202_6081_amd/csrc/kernels.hip", "paper_1202_6081_amd/csrc/node.hpp",
+                  "paper_1202_6081_amd/csrc/collide_d3q27.hpp",
                   "paper_1202_6081_amd/csrc/lattice.hpp", "paper_1202_6081_amd/csrc/kernels.hpp"]
 
 

@@ -341,49 +341,97 @@ CMLBM_HD void source_raw15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gr)
   guz += c * (Fz * (ux2 + uy2) + R(2) * uz * (Fu + Fv));
 }
 
+// shift15 with its multiply-adds as written.
+template <int AX, typename R>
+CMLBM_HD void shift15_as_written(R (&m)[15], R v) {
+  constexpr Groups15 G = groups15<AX>();
+  static_for<G.nt>([&](auto i) {
+    CMLBM_FMA_AS_WRITTEN
+    constexpr int a = G.t[decltype(i)::value][0], b = G.t[decltype(i)::value][1], c = G.t[decltype(i)::value][2];
+    const R nb = fma_r(v, m[a], m[b]);
+    m[c] = fma_r(v, m[b] + nb, m[c]);
+    m[b] = nb;
+  });
+  static_for<G.np>([&](auto i) {
+    CMLBM_FMA_AS_WRITTEN
+    constexpr int a = G.p[decltype(i)::value][0], b = G.p[decltype(i)::value][1];
+    m[b] = fma_r(v, m[a], m[b]);
+  });
+}
+
+// The multiply-adds of the collision are those written and no others, as in D3Q27's.
 template <typename R>
 CMLBM_HD void collide15(R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& p) {
+  CMLBM_FMA_AS_WRITTEN
   R m[15];
   raw_moments15(f, m);
   const R rho = m[M0];
   const R inv_rho = recip(rho);
-  // (explicit fused multiply-adds, as in the D3Q27 collision)
   const R ux = fma_r(R(0.5), Fx, m[MX]) * inv_rho;
   const R uy = fma_r(R(0.5), Fy, m[MY]) * inv_rho;
   const R uz = fma_r(R(0.5), Fz, m[MZ]) * inv_rho;
-  // raw moments of h = f + S, then central moments about u
+  // raw moments of h = f + S (source_raw15), then central moments about u
   {
-    R rs[15];
-    source_raw15(Fx, Fy, Fz, ux, uy, uz, rs);
-#pragma unroll
-    for (int k = 1; k < 15; ++k) m[k] += rs[k];
+    const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
+    const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
+    const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
+    m[MX] += Fx;
+    m[MY] += Fy;
+    m[MZ] += Fz;
+    m[MXY] += fma_r(Fx, uy, Fy * ux);
+    m[MXZ] += fma_r(Fx, uz, Fz * ux);
+    m[MYZ] += fma_r(Fz, uy, Fy * uz);
+    m[MXX] = fma_r(R(2), Fu, m[MXX]);
+    m[MYY] = fma_r(R(2), Fv, m[MYY]);
+    m[MZZ] = fma_r(R(2), Fw, m[MZZ]);
+    const R cx = fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1), cy = fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1);
+    const R cz = fma_r(R(3), uz2, xy2) - R(1);
+    m[MXYY] = fma_r(R(0.5), fma_r(ux + ux, fma_r(Fy, uy, Fw), Fx * cx), m[MXYY]);
+    m[MXXY] = fma_r(R(0.5), fma_r(uy + uy, fma_r(Fx, ux, Fw), Fy * cy), m[MXXY]);
+    m[MXXZ] = fma_r(R(0.5), fma_r(uz + uz, fma_r(Fy, uy, Fu), Fz * cz), m[MXXZ]);
+    m[MXYZ] += fma_r(uy, Fz * ux, fma_r(uz, Fx * uy, uz * (Fy * ux)));
+    m[MXXYY] = fma_r(R(2.0 / 3.0), fma_r(Fw, xy2, fma_r(Fu, yz2, Fv * xz2)), m[MXXYY]);
   }
-  shift15<0>(m, ux, R(-1));
-  shift15<1>(m, uy, R(-1));
-  shift15<2>(m, uz, R(-1));
+  shift15_as_written<0>(m, -ux);
+  shift15_as_written<1>(m, -uy);
+  shift15_as_written<2>(m, -uz);
   // relaxation; density and the first central moments (F/2) are conserved
   const R d1 = p.wc[7] * (m[MXX] - m[MYY]);
-  const R d2 = p.wc[8] * (m[MXX] + m[MYY] - R(2) * m[MZZ]);
-  const R t9 = p.wc[9] * (m[MXX] + m[MYY] + m[MZZ]) + p.w[9] * rho;
-  const R txx = (R(2) * t9 + d2 + R(3) * d1) * R(1.0 / 6.0);
-  const R tyy = (R(2) * t9 + d2 - R(3) * d1) * R(1.0 / 6.0);
-  const R tzz = (t9 - d2) * R(1.0 / 3.0);
+  const R xy2 = m[MXX] + m[MYY], D2 = fma_r(R(-2), m[MZZ], xy2);
+  const R t9 = fma_r(p.w[9], rho, p.wc[9] * (xy2 + m[MZZ]));
+  const R td = fma_r(p.wc[8], D2, t9 + t9);
+  const R txx = fma_r(d1, R(3), td) * R(1.0 / 6.0);
+  const R tyy = fma_r(d1, R(-3), td) * R(1.0 / 6.0);
+  const R tzz = fma_r(-p.wc[8], D2, t9) * R(1.0 / 3.0);
+  const R sm = p.per_mass ? inv_rho : R(1);
+  const R xxyy = fma_r(p.wc[14], m[MXXYY], p.w[14] * (txx * tyy * sm));
+  // ... and back to raw moments along z and y (shift15), with the relaxed
+  // moments that are products fused into the sums that use them
+  const R half = R(0.5), hx = half * Fx, hy = half * Fy, hz = half * Fz;
+  const R mxy = p.wc[4] * m[MXY];
+  const R z1 = fma_r(half, Fz, rho * uz), z2 = fma_r(uz, hz + z1, tzz);
+  const R xz = fma_r(hx, uz, p.wc[5] * m[MXZ]), yz = fma_r(hy, uz, p.wc[6] * m[MYZ]);
+  const R xyz = fma_r(uz, mxy, p.wc[13] * m[MXYZ]), xxz = fma_r(p.wc[12], m[MXXZ], uz * txx);
+  const R y1 = fma_r(half, Fy, rho * uy), y2 = fma_r(uy, hy + y1, tyy);
+  const R xy = fma_r(hx, uy, mxy), xyy = fma_r(uy, fma_r(p.wc[4], m[MXY], xy), p.wc[10] * m[MXYY]);
+  const R xxy = fma_r(p.wc[11], m[MXXY], uy * txx);
+  m[MXXYY] = fma_r(uy, fma_r(p.wc[11], m[MXXY], xxy), xxyy);
   m[M0] = rho;
-  m[MX] = R(0.5) * Fx;
-  m[MY] = R(0.5) * Fy;
-  m[MZ] = R(0.5) * Fz;
-  m[MXY] *= p.wc[4];
-  m[MXZ] *= p.wc[5];
-  m[MYZ] *= p.wc[6];
+  m[MX] = hx;
+  m[MY] = y1;
+  m[MZ] = z1;
   m[MXX] = txx;
-  m[MYY] = tyy;
-  m[MZZ] = tzz;
-  m[MXYY] *= p.wc[10];
-  m[MXXY] *= p.wc[11];
-  m[MXXZ] *= p.wc[12];
-  m[MXYZ] *= p.wc[13];
-  m[MXXYY] = p.wc[14] * m[MXXYY] + p.w[14] * (txx * tyy * (p.per_mass ? inv_rho : R(1)));
-  populations_from_central15(m, ux, uy, uz, f);
+  m[MYY] = y2;
+  m[MZZ] = z2;
+  m[MXY] = xy;
+  m[MXZ] = xz;
+  m[MYZ] = fma_r(uy, z1, yz);
+  m[MXYY] = xyy;
+  m[MXXY] = xxy;
+  m[MXXZ] = xxz;
+  m[MXYZ] = fma_r(uy, xz, xyz);
+  shift15_as_written<0>(m, ux);
+  populations_from_raw15(m, f);
 }
 
 // Initial transformed populations fbar = f^eq(rho, u) - S/2: f^eq has the

@@ -366,6 +366,107 @@ CMLBM_HD void first_pass27(R (&m)[27], R Fx, R Fy, R Fz, R& rho, R& ux, R& uy, R
   }
 }
 
+// In a function that starts with this, the multiply-adds are those written
+// (fma_r) and no others.  Several sums of the relaxation have two products of
+// which either could be fused; left to the compiler, the choice, and with it the
+// rounding, depends on the code around the collision, and the kernels that run it
+// (two buffers, in place, two steps in one pass) would not agree bit for bit.
+#define CMLBM_FMA_AS_WRITTEN _Pragma("clang fp contract(off)")
+
+template <int AXIS, typename R>
+CMLBM_HD void shift_pass_as_written(R (&m)[27], R u) {
+  CMLBM_FMA_AS_WRITTEN
+  constexpr int S = line_stride<AXIS>();
+#pragma unroll
+  for (int l = 0; l < 9; ++l) {
+    const int o = line_base<AXIS>(l);
+    const R k1 = fma_r(-u, m[o], m[o + S]);
+    m[o + 2 * S] = fma_r(-u, m[o + S] + k1, m[o + 2 * S]);
+    m[o + S] = k1;
+  }
+}
+
+// The relaxation of relax27 and the inverse pass along x (inv_pass<0, false>) in
+// one, from central moments to populations along x.  A relaxed moment that is a
+// product is fused into the sums that use it where it can be.
+template <typename R>
+CMLBM_HD void relax_unshift_x27(R (&m)[27], R rho, R inv_rho, R ux, R Fx, R Fy, R Fz, const Rates<R>& p) {
+  CMLBM_FMA_AS_WRITTEN
+  constexpr R third = R(1.0 / 3.0), sixth = R(1.0 / 6.0), half = R(0.5);
+  // second order, diagonal: kxx = sixth X, kyy = sixth Y, kzz = third Z
+  const R xx = m[K3(2, 0, 0)], yy = m[K3(0, 2, 0)], zz = m[K3(0, 0, 2)];
+  const R D1 = xx - yy, xy2 = yy + xx, D2 = fma_r(R(-2), zz, xy2);
+  const R t = fma_r(p.w[9], rho, p.wc[9] * (zz + xy2));
+  const R d1 = p.wc[7] * D1, td = fma_r(p.wc[8], D2, t + t);
+  const R X = fma_r(d1, R(3), td), Y = fma_r(d1, R(-3), td), Z = fma_r(-p.wc[8], D2, t);
+  const R kxx = X * sixth, kyy = Y * sixth, kzz = Z * third;
+  // third order pairs (twice the moments)
+  auto pair = [&](int i, int j, int bs, int bd) {
+    CMLBM_FMA_AS_WRITTEN
+    const R s = m[i] + m[j], d = p.wc[bd] * (m[i] - m[j]);
+    m[i] = fma_r(p.wc[bs], s, d);
+    m[j] = fma_r(p.wc[bs], s, -d);
+  };
+  pair(K3(1, 2, 0), K3(1, 0, 2), 10, 13);
+  pair(K3(2, 1, 0), K3(0, 1, 2), 11, 14);
+  pair(K3(2, 0, 1), K3(0, 2, 1), 12, 15);
+  // fourth order, diagonal: m022 = third T
+  const R sm = p.per_mass ? inv_rho : R(1);
+  const R kxy = kxx * kyy, kyz = kzz * kyy;
+  const R axz = sm * (kzz * kxx), ayz = sm * kyz;
+  const R axy_xz = fma_r(sm, kxy, axz);
+  const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
+  const R q1 = fma_r(p.wc[17], C + (A + B), p.w[17] * fma_r(sm, kyz, axy_xz));
+  const R q2 = fma_r(p.wc[18], fma_r(R(-2), C, A + B), p.w[18] * fma_r(R(-2), ayz, axy_xz));
+  const R q3 = fma_r(p.wc[19], A - B, p.w[19] * fma_r(sm, kxy, -axz));
+  const R ab = fma_r(R(2), q1, q2), T = q1 - q2;
+  const R m220 = half * fma_r(ab, third, q3), m202 = half * fma_r(ab, third, -q3), m022 = third * T;
+  // sixth order
+  const R m222 = fma_r(p.wc[26], m[K3(2, 2, 2)], p.w[26] * ((sm * sm) * (kzz * kxy)));
+  // the lines along x: (raw first moment, raw second, rest) -> (p_-, p_0, p_+)
+  auto line = [&](int o, R r1, R r2, R rest) {
+    m[o] = r2 - r1;
+    m[o + 9] = rest;
+    m[o + 18] = r2 + r1;
+  };
+  {
+    const R r1 = fma_r(half, Fx, rho * ux), r2 = fma_r(ux, fma_r(half, Fx, r1), kxx);
+    line(K3(0, 0, 0), r1, r2, rho - r2);
+  }
+  auto first = [&](int o, R F, R w, R m1, R m2) {        // m0 = F/2, m1 a product
+    CMLBM_FMA_AS_WRITTEN
+    const R r1 = fma_r(half * F, ux, w * m1), r2 = fma_r(ux, fma_r(w, m1, r1), m2);
+    line(o, r1, r2, fma_r(F, half, -r2));
+  };
+  first(K3(0, 0, 1), Fz, p.wc[5], m[K3(1, 0, 1)], half * m[K3(2, 0, 1)]);
+  first(K3(0, 1, 0), Fy, p.wc[4], m[K3(1, 1, 0)], half * m[K3(2, 1, 0)]);
+  {
+    const R m011 = m[K3(0, 1, 1)], m111 = m[K3(1, 1, 1)];
+    const R r1 = fma_r(ux, p.wc[6] * m011, p.wc[16] * m111);
+    const R r2 = fma_r(ux, fma_r(p.wc[16], m111, r1), p.wc[20] * m[K3(2, 1, 1)]);
+    line(K3(0, 1, 1), r1, r2, fma_r(p.wc[6], m011, -r2));
+  }
+  auto square = [&](int o, R m0, R K, R f, R S, R m2) {  // m0 = f K, m1 = S/2
+    CMLBM_FMA_AS_WRITTEN
+    const R r1 = fma_r(half, S, ux * m0), r2 = fma_r(ux, fma_r(half, S, r1), m2);
+    line(o, r1, r2, fma_r(K, f, -r2));
+  };
+  square(K3(0, 0, 2), kzz, Z, third, m[K3(1, 0, 2)], m202);
+  square(K3(0, 2, 0), kyy, Y, sixth, m[K3(1, 2, 0)], m220);
+  auto odd = [&](int o, R w1, R m1, R w2, R m2) {        // m0 = S/2, m1 and m2 products
+    CMLBM_FMA_AS_WRITTEN
+    const R S = m[o], r1 = fma_r(w1, m1, ux * (half * S)), r2 = fma_r(w2, m2, ux * fma_r(w1, m1, r1));
+    line(o, r1, r2, fma_r(S, half, -r2));
+  };
+  odd(K3(0, 2, 1), p.wc[21], m[K3(1, 2, 1)], p.wc[25], m[K3(2, 2, 1)]);
+  odd(K3(0, 1, 2), p.wc[22], m[K3(1, 1, 2)], p.wc[24], m[K3(2, 1, 2)]);
+  {
+    const R m122 = m[K3(1, 2, 2)];
+    const R r1 = fma_r(p.wc[23], m122, ux * m022), r2 = fma_r(ux, fma_r(p.wc[23], m122, r1), m222);
+    line(K3(0, 2, 2), r1, r2, fma_r(T, third, -r2));
+  }
+}
+
 // Full collision: cube-ordered pre-collision populations in, post-collision out.
 template <typename R>
 CMLBM_HD void collide27(R (&m)[27], R Fx, R Fy, R Fz, const Rates<R>& p) {
@@ -379,14 +480,13 @@ CMLBM_HD void collide27(R (&m)[27], R Fx, R Fy, R Fz, const Rates<R>& p) {
   const R ux = fma_r(R(0.5), Fx, m[K3(1, 0, 0)]) * inv_rho;
   const R uy = fma_r(R(0.5), Fy, m[K3(0, 1, 0)]) * inv_rho;
   const R uz = fma_r(R(0.5), Fz, m[K3(0, 0, 1)]) * inv_rho;
-  shift_pass<0>(m, ux);
-  shift_pass<1>(m, uy);
-  shift_pass<2>(m, uz);
-  relax27(m, rho, inv_rho, Fx, Fy, Fz, p);
+  shift_pass_as_written<0>(m, ux);
+  shift_pass_as_written<1>(m, uy);
+  shift_pass_as_written<2>(m, uz);
   // the three inverse passes without their halvings, then population e scaled
   // by 2^-(number of nonzero components of e) (one multiply each, which a
   // 16-bit store fuses with its subtraction of the rest weight)
-  inv_pass<0, false>(m, ux);
+  relax_unshift_x27(m, rho, inv_rho, ux, Fx, Fy, Fz, p);
   inv_pass<1, false>(m, uy);
   inv_pass<2, false>(m, uz);
 #pragma unroll
