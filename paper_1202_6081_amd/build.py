@@ -6,15 +6,16 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcmlbm.so")
 
-SOURCES = ["api.cpp", "kernels.hip", "checks.hip"]
+SOURCES = ["kernels.hip", "step2.hip", "checks.hip", "api.cpp"]
 # -packed-fp32-ops: no v_pk_* FP32 instructions are generated.
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 
@@ -27,15 +28,23 @@ def hipcc():
 
 
 def build(verbose=False):
+    """Compile every source (at the same time: kernels.hip takes a minute) and link."""
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libcmlbm.so")
+    with tempfile.TemporaryDirectory() as work:
+        objs = [os.path.join(work, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+        cmds = [[hipcc(), *FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", os.path.join(CSRC, s), "-o", o]
+                for s, o in zip(SOURCES, objs)]
+        if verbose:
+            print("\n".join(" ".join(c) for c in cmds), flush=True)
+        running = [subprocess.Popen(c, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for c in cmds]
+        said = [p.communicate()[0] for p in running]
+        if any(p.returncode for p in running):
+            sys.stderr.write("".join(said))
+            raise RuntimeError("hipcc failed building libcmlbm.so")
+        res = subprocess.run([hipcc(), *FLAGS, "-shared", *objs, "-o", tmp], capture_output=True, text=True)
+        if res.returncode != 0:
+            sys.stderr.write(res.stdout + res.stderr)
+            raise RuntimeError("hipcc failed linking libcmlbm.so")
     os.replace(tmp, LIB)
     return LIB
 

@@ -51,6 +51,14 @@ struct StepArgs {
   RowMap rm;
 };
 
+// Tiles of the two-steps-in-one-pass kernel, in each run of zlen planes along z:
+// `main` tiles over the first nbx blocks of 64 nodes along x, and `tail` tiles
+// of tail_rows rows over a short last block.
+struct Tiles2 {
+  uint32_t nbx, main, tail, tail_rows, zlen;
+  Divider bx, all, tail_width;   // by nbx, by main + tail, by the tail's columns with its halo
+};
+
 template <typename R>
 struct AuxArgs {
   Geom g;
@@ -75,6 +83,10 @@ struct AdjArgs {
 
 // prec: 0 FP64, 1 FP32, 2 FP32 compute / FP16 deviation storage, 3 BF16 deviations.
 hipError_t launch_step(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, hipStream_t st);
+// Two steps from a.fin to a.fout in one pass (no totals), the same populations as
+// two launch_step calls; step2_pays: whether that is the faster way.
+bool step2_pays(int q, int prec, const Geom& g, bool walls);
+hipError_t launch_step2(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, hipStream_t st);
 hipError_t launch_gather(int q, int prec, const AuxArgs<double>& a64, const AuxArgs<float>& a32, hipStream_t st);
 // Population buffer (blocked layout) <-> full populations in compute type,
 // structure of arrays [Q][N]; to_soa selects the direction.
