@@ -672,12 +672,12 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
 #pragma unroll
   for (int m = 4; m < 7; ++m) {
     gc[m] = p.wc[m] * gt[m];
-    gw[m] -= c[m] * gt[m];
+    sub_product(gw, m, c[m], gt[m]);
   }
 #pragma unroll
   for (int m = 10; m < 14; ++m) {
     gc[m] = p.wc[m] * gt[m];
-    gw[m] -= c[m] * gt[m];
+    sub_product(gw, m, c[m], gt[m]);
   }
   R gtxx = gt[7], gtyy = gt[8];
   const R gtzz = gt[9];
@@ -685,7 +685,7 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
     const R G = gt[14];
     const R A = txx * tyy * sm;
     gc[14] = p.wc[14] * G;
-    gw[14] += (A - c[14]) * G;
+    add_product(gw, 14, A - c[14], G);
     const R gA = p.w[14] * G;
     if (pm) grho -= sm * A * gA;
     gtxx += gA * tyy * sm;
@@ -695,9 +695,9 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
     const R gt9 = (gtxx + gtyy) * R(1.0 / 3.0) + gtzz * R(1.0 / 3.0);
     const R gd2 = (gtxx + gtyy) * R(1.0 / 6.0) - gtzz * R(1.0 / 3.0);
     const R gd1 = R(0.5) * (gtxx - gtyy);
-    gw[7] -= (c[7] - c[8]) * gd1;
-    gw[8] -= (c[7] + c[8] - R(2) * c[9]) * gd2;
-    gw[9] += (rho - (c[7] + c[8] + c[9])) * gt9;
+    sub_product(gw, 7, c[7] - c[8], gd1);
+    sub_product(gw, 8, c[7] + c[8] - R(2) * c[9], gd2);
+    add_product(gw, 9, rho - (c[7] + c[8] + c[9]), gt9);
     grho += p.w[9] * gt9;
     const R gD1 = p.wc[7] * gd1, gD2 = p.wc[8] * gd2, gT = p.wc[9] * gt9;
     gc[7] = gD1 + gD2 + gT;

@@ -496,10 +496,21 @@ CMLBM_HD void collide27(R (&m)[27], R Fx, R Fy, R Fz, const Rates<R>& p) {
   }
 }
 
+// Adds x g to entry b of a rate-adjoint accumulator, or subtracts it (an array or
+// anything whose operator[] yields an R&; accumulators that keep the factors
+// overload these).
+template <typename W, typename R>
+CMLBM_HD void add_product(W& gw, int b, R x, R g) {
+  gw[b] += x * g;
+}
+template <typename W, typename R>
+CMLBM_HD void sub_product(W& gw, int b, R x, R g) {
+  gw[b] -= x * g;
+}
+
 // Adjoint of relax27.  m: pre-relaxation central moments (unchanged).  g: on
 // entry the adjoint of the relaxed moments, on exit the adjoint of m.  Adds to
-// grho, gF*, gw[b] (adjoint of omega_b, b = 4..26; gw is an array or any
-// accumulator whose operator[] yields an R&).
+// grho, gF* and, through add_product, gw[b] (adjoint of omega_b, b = 4..26).
 template <int PM = -1, typename R, typename W>
 CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27], R& grho,
                                             R& gFx, R& gFy, R& gFz, W& gw) {
@@ -520,7 +531,7 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
     const R G = g[K3(2, 2, 2)];
     const R s2 = sm * sm;
     const R P = kxx * kyy * kzz * s2;
-    gw[26] += (P - m[K3(2, 2, 2)]) * G;
+    add_product(gw, 26, P - m[K3(2, 2, 2)], G);
     const R gP = p.w[26] * G;
     if (pm) grho -= R(2) * sm * P * gP;
     const R gPs = gP * s2;
@@ -533,7 +544,7 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
 #define CMLBM_SCALE_ADJ(I, B)         \
   {                                   \
     const R G = g[I];                 \
-    gw[B] -= m[I] * G;                \
+    sub_product(gw, B, m[I], G);     \
     g[I] = p.wc[B] * G;               \
   }
   CMLBM_SCALE_ADJ(K3(1, 2, 2), 23)
@@ -553,9 +564,9 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
     const R gq3 = R(0.5) * (gA - gB);
     const R gq1 = (gC + R(2) * gab) * R(1.0 / 3.0);
     const R gq2 = (gab - gC) * R(1.0 / 3.0);
-    gw[17] += (a1 - Q1) * gq1;
-    gw[18] += (a2 - Q2) * gq2;
-    gw[19] += (a3 - Q3) * gq3;
+    add_product(gw, 17, a1 - Q1, gq1);
+    add_product(gw, 18, a2 - Q2, gq2);
+    add_product(gw, 19, a3 - Q3, gq3);
     const R ga1 = p.w[17] * gq1, ga2 = p.w[18] * gq2, ga3 = p.w[19] * gq3;
     const R gQ1 = p.wc[17] * gq1, gQ2 = p.wc[18] * gq2, gQ3 = p.wc[19] * gq3;
     const R gaxy = ga1 + ga2 + ga3, gaxz = ga1 + ga2 - ga3, gayz = ga1 - R(2) * ga2;
@@ -573,8 +584,8 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
   {                                                     \
     const R gs = R(0.5) * (g[IA] + g[IB]);              \
     const R gd = R(0.5) * (g[IA] - g[IB]);              \
-    gw[BS] -= (m[IA] + m[IB]) * gs;                     \
-    gw[BD] -= (m[IA] - m[IB]) * gd;                     \
+    sub_product(gw, BS, m[IA] + m[IB], gs);          \
+    sub_product(gw, BD, m[IA] - m[IB], gd);          \
     const R a = p.wc[BS] * gs, b = p.wc[BD] * gd;       \
     g[IA] = a + b;                                      \
     g[IB] = a - b;                                      \
@@ -589,9 +600,9 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
     const R gt = (Gx + Gy) * R(1.0 / 3.0) + Gz * R(1.0 / 3.0);
     const R gd2 = (Gx + Gy) * R(1.0 / 6.0) - Gz * R(1.0 / 3.0);
     const R gd1 = R(0.5) * (Gx - Gy);
-    gw[7] -= D1 * gd1;
-    gw[8] -= D2 * gd2;
-    gw[9] += (rho - T) * gt;
+    sub_product(gw, 7, D1, gd1);
+    sub_product(gw, 8, D2, gd2);
+    add_product(gw, 9, rho - T, gt);
     grho += p.w[9] * gt;
     const R gD1 = p.wc[7] * gd1, gD2 = p.wc[8] * gd2, gT = p.wc[9] * gt;
     g[K3(2, 0, 0)] = gD1 + gD2 + gT;

@@ -764,11 +764,42 @@ __device__ __forceinline__ uint64_t per_item(uint64_t n) {
   return n;
 }
 
+// SPLIT: the same sums with eight times the wavefronts, for lattices too small
+// to fill the CUs otherwise (64^3: 512 wavefronts for 1024 SIMDs, each doing the
+// gathers and collisions of eight nodes one after the other).  A block has eight
+// wavefronts and takes the row segments of one block of the other form, 64 lanes
+// of them, one segment per wavefront.  The other form's sums over a thread's
+// nodes are multiply-adds in the arithmetic's precision, in their order: here the
+// wavefronts leave the factors in LDS and the block goes through them in that
+// order afterwards, for the same sums.  (FP64 leaves the products; the sums may
+// differ in the last bit.)  Adjoint step with its reduction, 64^3 D3Q27 FP32: 61.4
+// -> 28.2 us (the reduction in one launch instead of two is 9.7 of that), 32^3 60.6
+// -> 13.6, 96 x 50 x 50 with walls 94.3 -> 42.2, 64^3 D3Q15 47.3 -> 16.8.
+constexpr int kAdjSplitBlock = 512;
+template <int NB, typename R>
+struct Products {
+  R* p;   // FP32: the factors x, then, NB columns on, g; FP64: their products
+};
+template <int NB, typename R>
+__device__ __forceinline__ void add_product(Products<NB, R>& w, int b, R x, R g) {
+  if constexpr (sizeof(R) == 8) {
+    w.p[(b - 4) * kAdjSplitBlock] = x * g;
+  } else {
+    w.p[(b - 4) * kAdjSplitBlock] = x;
+    w.p[(NB + b - 4) * kAdjSplitBlock] = g;
+  }
+}
+template <int NB, typename R>
+__device__ __forceinline__ void sub_product(Products<NB, R>& w, int b, R x, R g) {
+  add_product(w, b, -x, g);
+}
+
 // PM: attractor form compiled in (0 literal, 1 per unit mass); the host picks
 // the instance that matches the rates' per_mass flag.
-template <int Q, class ST, bool MASK, int PM>
-__global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(adjoint_waves<ST, MASK>()))) void k_adjoint(
-    AdjArgs<typename ST::R> args, double* partials) {
+template <int Q, class ST, bool MASK, int PM, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kAdjSplitBlock : kAdjBlock)
+    __attribute__((amdgpu_waves_per_eu(SPLIT ? 1 : adjoint_waves<ST, MASK>()))) void k_adjoint(
+        AdjArgs<typename ST::R> args, double* partials, uint32_t segment) {
   using R = typename ST::R;
   using T = typename ST::T;
   const Geom g = args.g;
@@ -776,25 +807,40 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(adjoi
   // Per-thread running sums over the (few) nodes this thread visits, in LDS to
   // keep registers for the collision: dL/domega_b for b = 4..26; uF = dL/dF
   // for a uniform force.
-  __shared__ R wsh[23 * kAdjBlock];
-  LdsColumn<R> wacc{wsh + threadIdx.x};
+  // (SPLIT: the factors and force gradients of each node)
+  __shared__ R wsh[SPLIT ? (sizeof(R) == 8 ? Q - 4 : 2 * (Q - 4)) * kAdjSplitBlock : 23 * kAdjBlock];
+  __shared__ R fsh[SPLIT ? 3 * kAdjSplitBlock : 1];
+  std::conditional_t<SPLIT, Products<Q - 4, R>, LdsColumn<R>> wacc{wsh + threadIdx.x};
+  if constexpr (SPLIT) {
 #pragma unroll
-  for (int b = 4; b < 27; ++b) wacc[b] = R(0);   // (b >= Q stays zero)
+    for (int b = 0; b < (sizeof(R) == 8 ? Q - 4 : 2 * (Q - 4)); ++b) wsh[b * kAdjSplitBlock + threadIdx.x] = R(0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) fsh[i * kAdjSplitBlock + threadIdx.x] = R(0);
+  } else {
+#pragma unroll
+    for (int b = 4; b < 27; ++b) wacc[b] = R(0);   // (b >= Q stays zero)
+  }
   R uF[3] = {R(0), R(0), R(0)};
-  const uint32_t nseg = (nx + blockDim.x - 1) / blockDim.x;
+  const uint32_t bx = SPLIT ? segment : blockDim.x;   // nodes of a row segment
+  const uint32_t nseg = (nx + bx - 1) / bx;
   const uint32_t items = nseg * uint32_t(g.ny) * uint32_t(g.nz);
   // Row segments are dealt to the eight XCDs in contiguous runs; inside its
   // run, an XCD's blocks take the segments in turn (its block b: b, b + per,
   // b + 2 per, ...), so that the blocks running at one time work on adjacent
   // segments and find the cache lines they share still in the XCD's L2.  (The
   // grid is a multiple of 8; consecutive block ids go to the XCDs in turn.)
-  const uint32_t per = gridDim.x >> 3;
+  // SPLIT: the block xcd + 8 n of the other form is here the blocks
+  // xcd + 8 (n cols + col) of 64 lanes each, wavefront k taking segment k.
+  const uint32_t cols = SPLIT ? bx >> 6 : 1u, blk = blockIdx.x >> 3, n = SPLIT ? blk / cols : blk;
+  const uint32_t per = (gridDim.x >> 3) / cols;
   const uint32_t run = (items + 7u) >> 3;
   const uint32_t i0 = (blockIdx.x & 7u) * run;
   const uint32_t i1 = min(items, i0 + run);
-  for (uint32_t it = i0 + (blockIdx.x >> 3); it < i1; it += per) {
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane_x = SPLIT ? (blk - n * cols) * 64u + (threadIdx.x & 63u) : threadIdx.x;
+  for (uint32_t it = i0 + n + (SPLIT ? wave * per : 0u); it < i1; it += SPLIT ? items : per) {
     const uint32_t row = it / nseg;
-    const uint32_t x = (it - row * nseg) * blockDim.x + threadIdx.x;
+    const uint32_t x = (it - row * nseg) * bx + lane_x;
     if (x >= nx) continue;
     const uint32_t rowB = nx * uint32_t(sizeof(R)), xB = x * uint32_t(sizeof(R));   // one row of a [Q][N] plane
     const Coord c{int(x), int(row % uint32_t(g.ny)), int(row / uint32_t(g.ny))};
@@ -866,6 +912,12 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(adjoi
       Fy = R(args.force.uni[1]);
       Fz = R(args.force.uni[2]);
     }
+    if constexpr (SPLIT) {
+      // (taken as new here: the products with F are then fused as in the other form)
+      asm volatile("" : "+v"(Fx));
+      asm volatile("" : "+v"(Fy));
+      asm volatile("" : "+v"(Fz));
+    }
     R gFx = R(0), gFy = R(0), gFz = R(0);
     if constexpr (Q == 27) {
       R s[27];
@@ -886,25 +938,65 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(adjoi
         const __amdgpu_buffer_rsrc_t rd = array_rsrc(args.dLdF + uint64_t(k) * N + uint64_t(row) * nx, nx * 8u);
         buf_store<kAdjAux>(buf_load<double>(rd, xD, 0u) + sc * gF[k], rd, xD, 0u);
       }
+    } else if constexpr (SPLIT) {
+      const R gF[3] = {gFx, gFy, gFz};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) fsh[i * kAdjSplitBlock + threadIdx.x] = gF[i];
     } else {
       uF[0] += gFx;
       uF[1] += gFy;
       uF[2] += gFz;
     }
   }
-  double v[26];
+  if constexpr (SPLIT) {
+    constexpr uint32_t B = kAdjSplitBlock, NB = Q - 4;
+    __syncthreads();
+    for (uint32_t c = wave; c < 26u; c += 8u) {
+      const uint32_t o = threadIdx.x & 63u;
+      R acc = R(0);
+      if (c < NB) {
 #pragma unroll
-  for (int b = 4; b < 27; ++b) v[b - 4] = b < Q ? double(wacc[b]) : 0.0;
-  __syncthreads();
-  v[23] = double(uF[0]) * double(args.force.scale);
-  v[24] = double(uF[1]) * double(args.force.scale);
-  v[25] = double(uF[2]) * double(args.force.scale);
-  __shared__ double sh[26 * 8];
-  block_sum<26>(v, sh);
-  if (threadIdx.x == 0) {
+        for (uint32_t k = 0; k < 8; ++k) {
+          if constexpr (sizeof(R) == 8)
+            acc += wsh[c * B + k * 64u + o];
+          else
+            acc = fma_r(wsh[c * B + k * 64u + o], wsh[(NB + c) * B + k * 64u + o], acc);
+        }
+      } else if (c >= 23u) {
 #pragma unroll
-    for (int i = 0; i < 26; ++i) partials[uint64_t(blockIdx.x) * 26 + i] = v[i];
+        for (uint32_t k = 0; k < 8; ++k) acc += fsh[(c - 23u) * B + k * 64u + o];
+      }
+      double s = c < 23u ? double(acc) : double(acc) * double(args.force.scale);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+      if (o == 0) partials[uint64_t(blockIdx.x) * 26 + c] = s;
+    }
+  } else {
+    double v[26];
+#pragma unroll
+    for (int b = 4; b < 27; ++b) v[b - 4] = b < Q ? double(wacc[b]) : 0.0;
+    __syncthreads();
+    v[23] = double(uF[0]) * double(args.force.scale);
+    v[24] = double(uF[1]) * double(args.force.scale);
+    v[25] = double(uF[2]) * double(args.force.scale);
+    __shared__ double sh[26 * 8];
+    block_sum<26>(v, sh);
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int i = 0; i < 26; ++i) partials[uint64_t(blockIdx.x) * 26 + i] = v[i];
+    }
   }
+}
+
+// Adds the column sums of nrows rows of 26 partials to the outputs: columns 0 ..
+// nw - 1 to dLdw and, if dLdF is given, 23 .. 25 to it.
+__global__ __launch_bounds__(256) void k_adjoint_sums(const double* rows, int nrows, int nw, double* dLdw, double* dLdF) {
+  const int c = int(blockIdx.x) < nw ? int(blockIdx.x) : 23 + int(blockIdx.x) - nw;
+  double v[1] = {0};
+  for (int r = threadIdx.x; r < nrows; r += 256) v[0] += rows[uint64_t(r) * 26 + c];
+  __shared__ double sh[8];
+  block_sum<1>(v, sh);
+  if (threadIdx.x == 0) (c < 23 ? dLdw[c] : dLdF[c - 23]) += v[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -1195,7 +1287,9 @@ hipError_t static_scratch(double** out) {
 
 namespace {
 
-inline int adjoint_block(const Geom& g) { return g.nx < 256 ? ((g.nx + 63) / 64) * 64 : 256; }
+// Rows of adjoint partials that one block per column sums by itself: 32 loads a
+// thread at most.  (The two stages take 11.5 + 4.7 us at any small number.)
+constexpr int kOneStageRows = 8192;
 
 inline unsigned aux_grid(const Geom& g) {
   const uint64_t need = (g.N + kBlock - 1) / kBlock;
@@ -1331,29 +1425,42 @@ hipError_t init_impl(const Geom& g, const void* rho0, const void* u0, const Forc
   return hipGetLastError();
 }
 
+template <int Q, class ST, bool MASK, int PM>
+void adjoint_launch(const AdjArgs<typename ST::R>& a, double* partials, int nblk, hipStream_t st) {
+  const int bx = adjoint_block(a.g);
+  if (adjoint_split(Q, sizeof(typename ST::R) == 8, a.g))
+    hipLaunchKernelGGL((k_adjoint<Q, ST, MASK, PM, true>), dim3(nblk * (bx / 64)), dim3(kAdjSplitBlock), 0, st, a, partials,
+                       uint32_t(bx));
+  else
+    hipLaunchKernelGGL((k_adjoint<Q, ST, MASK, PM, false>), dim3(nblk), dim3(bx), 0, st, a, partials, uint32_t(bx));
+}
+
 template <int Q, class ST>
-hipError_t adjoint_impl(const AdjArgs<typename ST::R>& args, double* partials, int nblk, double* dLdomega,
+hipError_t adjoint_impl(const AdjArgs<typename ST::R>& a, double* partials, int nblk, double* dLdomega,
                         double* dLdF_uniform, hipStream_t st) {
-  const dim3 grid(nblk), block(adjoint_block(args.g));
-  const AdjArgs<typename ST::R>& a = args;
   if (a.rates.per_mass) {
     if (a.mask)
-      hipLaunchKernelGGL((k_adjoint<Q, ST, true, 1>), grid, block, 0, st, a, partials);
+      adjoint_launch<Q, ST, true, 1>(a, partials, nblk, st);
     else
-      hipLaunchKernelGGL((k_adjoint<Q, ST, false, 1>), grid, block, 0, st, a, partials);
+      adjoint_launch<Q, ST, false, 1>(a, partials, nblk, st);
   } else {
     if (a.mask)
-      hipLaunchKernelGGL((k_adjoint<Q, ST, true, 0>), grid, block, 0, st, a, partials);
+      adjoint_launch<Q, ST, true, 0>(a, partials, nblk, st);
     else
-      hipLaunchKernelGGL((k_adjoint<Q, ST, false, 0>), grid, block, 0, st, a, partials);
+      adjoint_launch<Q, ST, false, 0>(a, partials, nblk, st);
   }
-  // two stages: kReduceChunks blocks sum contiguous runs of block rows (all 26
-  // columns), then one block per column adds the chunk sums into the outputs
-  double* stage = partials + uint64_t(26) * uint64_t(nblk);
-  hipLaunchKernelGGL(k_reduce_chunks<26>, dim3(kReduceChunks), dim3(kBlock), 0, st, partials, uint64_t(nblk), stage);
-  hipLaunchKernelGGL(k_reduce_rows, dim3(Q - 4), dim3(kBlock), 0, st, stage, kReduceChunks, 26, dLdomega, 1);
-  if (dLdF_uniform)
-    hipLaunchKernelGGL(k_reduce_rows, dim3(3), dim3(kBlock), 0, st, stage + 23, kReduceChunks, 26, dLdF_uniform, 1);
+  // Many rows of partials go in two stages: kReduceChunks blocks sum contiguous
+  // runs of rows (all 26 columns), then one block per column the chunk sums.
+  const double* rows = partials;
+  int nrows = adjoint_rows(Q, sizeof(typename ST::R) == 8, a.g);
+  if (nrows > kOneStageRows) {
+    double* stage = partials + uint64_t(26) * uint64_t(nrows);
+    hipLaunchKernelGGL(k_reduce_chunks<26>, dim3(kReduceChunks), dim3(kBlock), 0, st, partials, uint64_t(nrows), stage);
+    rows = stage;
+    nrows = kReduceChunks;
+  }
+  hipLaunchKernelGGL(k_adjoint_sums, dim3(Q - 4 + (dLdF_uniform ? 3 : 0)), dim3(256), 0, st, rows, nrows, Q - 4, dLdomega,
+                     dLdF_uniform);
   return hipGetLastError();
 }
 

@@ -126,17 +126,29 @@ hipError_t launch_init_adjoint(int q, int prec, const Geom& g, const void* u0, c
                                double* dLdF, double* partials, int nblk, hipStream_t st);
 
 // Blocks of the adjoint launch: a multiple of 8 (one share per XCD), each block
-// visiting about CMLBM_ADJ_ITEMS row segments (each thread at most that many
-// nodes, plus one).
-#ifndef CMLBM_ADJ_ITEMS
-#define CMLBM_ADJ_ITEMS 8
-#endif
+// visiting at most kAdjItems row segments (each thread that many nodes).
+constexpr uint64_t kAdjItems = 8;
+inline int adjoint_block(const Geom& g) { return g.nx < 256 ? ((g.nx + 63) / 64) * 64 : 256; }
 inline int adjoint_blocks(const Geom& g) {
-  const int bx = g.nx < 256 ? ((g.nx + 63) / 64) * 64 : 256;
+  const int bx = adjoint_block(g);
   const uint64_t items = uint64_t((g.nx + bx - 1) / bx) * uint64_t(g.ny) * uint64_t(g.nz);
-  uint64_t nb = (items + CMLBM_ADJ_ITEMS - 1) / CMLBM_ADJ_ITEMS;
+  uint64_t nb = (items + kAdjItems - 1) / kAdjItems;
   nb = ((nb + 7) / 8) * 8;
   return int(nb);
+}
+
+// Whether the adjoint takes the form with a wavefront per row segment (k_adjoint's
+// SPLIT) on a lattice, and the rows of partial sums that its blocks leave.  The
+// factors of D3Q27 take 100 KB of LDS, one block on a CU: the form wins while
+// there are a few blocks per CU (640 blocks, 96 x 50 x 50: 35 against 63 us; 2304,
+// 96^3: 96 against 87), in FP64 likewise (43 against 74; 2048, 256 x 64 x 64: 201
+// against 163).  D3Q15's take 51 KB in FP32 (2304 blocks: 46 against 57 us; 4096,
+// 128^3: 106 against 121).
+inline bool adjoint_split(int q, bool wide, const Geom& g) {
+  return adjoint_blocks(g) * (adjoint_block(g) / 64) <= (q == 15 && !wide ? 4096 : 1024);
+}
+inline int adjoint_rows(int q, bool wide, const Geom& g) {
+  return adjoint_blocks(g) * (adjoint_split(q, wide, g) ? adjoint_block(g) / 64 : 1);
 }
 
 constexpr int kTotalsBlocks = 2048;
