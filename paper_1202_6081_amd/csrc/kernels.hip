@@ -66,6 +66,33 @@ __global__ __launch_bounds__(CMLBM_STEP_BLOCK) void k_step(StepArgs<typename ST:
   }
 }
 
+// The step on lattices of few nodes in x, where a wavefront per row leaves most
+// lanes idle (61 of 64 at nx = 3) and the time is the dispatch and the loads of
+// such wavefronts: here the nodes are taken in a row, whatever rows they are in.
+// Every lane has addresses of its own, which costs a small grid about 1.2 us of latency;
+// see thin_pays.  A step, before -> after, in us: D3Q15 FP64 3 x 45 x 45 with
+// walls 7.1 -> 4.8, D3Q27 FP32 8 x 100 x 100 with walls 18.1 -> 10.5, D3Q27 BF16
+// 16 x 400 x 400 126.8 -> 70.0.
+template <int Q, class ST, bool MASK>
+__global__ __launch_bounds__(64) void k_step_thin(StepArgs<typename ST::R> args) {
+  using R = typename ST::R;
+  using T = typename ST::T;
+  const Geom g = args.g;
+  const uint32_t n = blockIdx.x * 64u + threadIdx.x;
+  if (n >= uint32_t(g.N) || (MASK && args.mask[n])) return;
+  const uint32_t nx = uint32_t(g.nx), row = args.rm.seg.div(n), x = n - row * nx;   // (rm.seg divides by nx)
+  const Stencil st(g, row_coord(args.rm, g, row, x), +1);
+  R f[Q], Fx, Fy, Fz;
+  pull<Q, ST, MASK>(static_cast<const T*>(args.fin), g, args.mask, st, row, x, f);
+  force_at(args.force, g.N, n, Fx, Fy, Fz);
+  collide<Q>(f, Fx, Fy, Fz, args.rates);
+  T v[Q];
+  encode_all<ST, Q>(f, v);
+  T* const out = static_cast<T*>(args.fout) + uint64_t(row) * nx * Q;
+#pragma unroll
+  for (int a = 0; a < Q; ++a) out[in_row<Q>(nx, a, x)] = v[a];
+}
+
 // ---------------------------------------------------------------------------
 // In-place step: one population buffer (the AA pattern of Bailey, Myre, Walsh,
 // Lilja and Saar, 2009)
@@ -1303,6 +1330,19 @@ inline RowMap row_map(const Geom& g, int bx) {
   return {nseg, Divider::of(nseg), Divider::of(uint32_t(g.ny))};
 }
 
+// Whether k_step_thin takes a step.  Measured against the row kernel (as a ratio of
+// its time, both lattices and all storage types, without and with walls): nx <= 8
+// wins from about 1600 rows (0.53 to 1.02; 1.3 at 135 rows, where a step is all latency),
+// nx = 12 and 16 from 4096 (0.65 to 1.02; 1.3 at 1024), nx = 24 and 32 only with
+// 40000 rows and for 16-bit storage (0.65 to 0.97; at 10000 rows up to 1.18),
+// where the wider types are at the memory's rate (1.03 at 32 x 400 x 400) and a
+// run takes two steps per pass.  From nx = 40 the row kernel is ahead.
+inline bool thin_pays(const Geom& g, bool narrow) {
+  if (g.nx > 32 || g.N >= (int64_t(1) << 31)) return false;
+  const int64_t rows = int64_t(g.ny) * g.nz;
+  return rows >= (g.nx <= 8 ? 1536 : g.nx <= 16 ? 4096 : 16384) && (g.nx <= 16 || narrow);
+}
+
 // The block partials of a step's totals summed into args.totals: in one launch
 // while a thread has few rows, else in two stages.  (Four steps of 32^3 FP64 with
 // totals, 1024 rows of partials: 77.7 -> 65.7 us.)
@@ -1323,6 +1363,15 @@ hipError_t step_impl(const StepArgs<typename ST::R>& args, hipStream_t st) {
   const dim3 grid = step_grid(args.g, bx);
   StepArgs<typename ST::R> a = args;
   a.rm = row_map(a.g, bx);
+  if (!a.partials && thin_pays(a.g, sizeof(typename ST::T) == 2)) {
+    a.rm = {uint32_t(a.g.nx), Divider::of(uint32_t(a.g.nx)), Divider::of(uint32_t(a.g.ny))};
+    const dim3 blocks(unsigned((a.g.N + 63) / 64));
+    if (a.mask)
+      hipLaunchKernelGGL((k_step_thin<Q, ST, true>), blocks, dim3(64), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_step_thin<Q, ST, false>), blocks, dim3(64), 0, st, a);
+    return hipGetLastError();
+  }
   if (!a.partials) {
     if (a.mask)
       hipLaunchKernelGGL((k_step<Q, ST, true, false>), grid, dim3(bx), 0, st, a);

@@ -426,8 +426,10 @@ hipError_t step2_impl(const StepArgs<typename ST::R>& a, hipStream_t st) {
 // weigh as much as the traffic saved: 64^3 takes 0.74-0.87 of the time of single
 // steps (0.88-0.92 with walls), 56^3 0.92-0.98 (1.03-1.13), 32^3 1.3-1.4; D3Q15 FP32
 // with walls, the lightest, 1.12 at 64^3, 1.02 at 64 x 96 x 64, 0.84 at 128 x 64 x 64.
-// Rows of a few nodes leave most lanes of the single steps idle, but not here:
-// 0.67-0.94 at 3 x 64 x 64, 0.20-0.37 at 3 x 300 x 300.
+// Rows that fill their last block badly leave lanes of the single steps idle, but
+// not here: 0.71-0.89 at 56 x 200 x 200.  (Up to nx = 8 single steps take
+// nodes whatever their rows, and are as fast below 2^18 nodes: 0.93-1.12 at 8 x 200 x 200
+// and 3 x 200 x 200, two steps over one.)
 // (The kernel's offsets within a plane of population rows have 32 bits.)
 bool step2_pays(int q, int prec, const Geom& g, bool walls) {
   if (prec > 1) return false;
@@ -435,7 +437,7 @@ bool step2_pays(int q, int prec, const Geom& g, bool walls) {
   const uint64_t lanes = uint64_t((g.nx + 63) / 64) * 64 * uint64_t(g.ny) * uint64_t(g.nz);
   const bool light = q == 15 && prec == 1 && walls;
   if (g.N >= (uint64_t(1) << (light ? 19 : 18))) return true;
-  return lanes >= (uint64_t(1) << (g.nx <= 8 ? 18 : 20));
+  return lanes >= (uint64_t(1) << 20) && g.nx > 8;
 }
 
 hipError_t launch_step2(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, hipStream_t st) {
