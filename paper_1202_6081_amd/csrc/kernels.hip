@@ -1275,10 +1275,19 @@ constexpr int kBlock = 256;
 // 3.7 + 2.0 for a step's four at any small number.)
 constexpr uint64_t kOneStageRows = 8192;
 
-inline int step_block(const Geom& g) {
-  int bx = CMLBM_STEP_BLOCK;
-  if (g.nx < bx) bx = ((g.nx + 63) / 64) * 64;
-  return bx;
+// Threads of a step's block where its number of blocks matters: a row of partial
+// totals each.
+inline int step_block(const Geom& g) { return even_block(g.nx, CMLBM_STEP_BLOCK); }
+
+// Threads of a plain step's block: the most of up to four wavefronts that leaves none
+// idle, which cost more than many small blocks do.  (D3Q27 FP32, us a step, blocks of
+// 256 -> this: 320 x 320 x 256 1130 -> 1013, 300 x 200 x 200 652 -> 539, 400 x 200 x 200
+// 685 -> 634; where four divide the row, blocks of one wavefront are up to 3% slower.)
+inline int plain_block(const Geom& g) {
+  const int waves = (g.nx + 63) / 64;
+  int k = waves < CMLBM_STEP_BLOCK / 64 ? waves : CMLBM_STEP_BLOCK / 64;
+  while (waves % k) --k;
+  return 64 * k;
 }
 
 inline dim3 step_grid(const Geom& g, int bx) {
@@ -1359,7 +1368,7 @@ void sum_totals(const StepArgs<R>& a, uint64_t rows, hipStream_t st) {
 
 template <int Q, class ST>
 hipError_t step_impl(const StepArgs<typename ST::R>& args, hipStream_t st) {
-  const int bx = step_block(args.g);
+  const int bx = args.partials ? step_block(args.g) : plain_block(args.g);
   const dim3 grid = step_grid(args.g, bx);
   StepArgs<typename ST::R> a = args;
   a.rm = row_map(a.g, bx);
@@ -1406,7 +1415,7 @@ void inplace_launch(const StepArgs<typename ST::R>& a, int parity, dim3 grid, in
 
 template <int Q, class ST>
 hipError_t inplace_impl(const StepArgs<typename ST::R>& args, int parity, hipStream_t st) {
-  const int bx = step_block(args.g);
+  const int bx = args.partials ? step_block(args.g) : plain_block(args.g);
   const dim3 grid = step_grid(args.g, bx);
   StepArgs<typename ST::R> a = args;
   a.rm = row_map(a.g, bx);
