@@ -213,13 +213,21 @@ CMLBM_HD void unshift_pass(R (&m)[27], R u) {
   }
 }
 
-// m: the output of shift_pass<AXIS> (central moments along AXIS).
-template <int AXIS, typename R>
+// m: the output of shift_pass<AXIS> (central moments along AXIS).  FUSE: a line
+// whose first product of the sum for gu is the fused one (-1: the compiler's choice
+// everywhere).
+template <int AXIS, int FUSE = -1, typename R>
 CMLBM_HD void shift_pass_adj(const R (&m)[27], R u, R (&g)[27], R& gu) {
   constexpr int S = line_stride<AXIS>();
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
     const int o = line_base<AXIS>(l);
+    if (l == FUSE) {
+      gu -= fma_r(m[o], g[o + S], R(2) * m[o + S] * g[o + 2 * S]);
+      R none = R(0);
+      shift_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], none);
+      continue;
+    }
     shift_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], gu);
   }
 }
@@ -508,6 +516,17 @@ CMLBM_HD void sub_product(W& gw, int b, R x, R g) {
   gw[b] -= x * g;
 }
 
+// The line of the y shift's adjoint whose products collide27_adj has to fuse in a given
+// way (see shift_pass_adj), by accumulator.
+template <typename W>
+struct FusedLine {
+  static constexpr int value = -1;
+};
+template <typename W>
+CMLBM_HD constexpr int fused_line() {
+  return FusedLine<W>::value;
+}
+
 // Adjoint of relax27.  m: pre-relaxation central moments (unchanged).  g: on
 // entry the adjoint of the relaxed moments, on exit the adjoint of m.  Adds to
 // grho, gF* and, through add_product, gw[b] (adjoint of omega_b, b = 4..26).
@@ -666,7 +685,7 @@ CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (
   // differentiated
   shift_pass_adj<2>(cm, uz, g, guz);
   unshift_pass<2>(cm, uz);
-  shift_pass_adj<1>(cm, uy, g, guy);
+  shift_pass_adj<1, fused_line<W>()>(cm, uy, g, guy);
   unshift_pass<1>(cm, uy);
   shift_pass_adj<0>(cm, ux, g, gux);
 

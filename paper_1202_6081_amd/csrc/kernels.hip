@@ -821,6 +821,14 @@ __device__ __forceinline__ void sub_product(Products<NB, R>& w, int b, R x, R g)
   add_product(w, b, -x, g);
 }
 
+// Without the running sums the compiler would fuse the other product of this line
+// than in the other form.  (So that lambda has the same bits in both, found by comparing the
+// two kernels' instructions product by product.)
+template <int NB>
+struct FusedLine<Products<NB, float>> {
+  static constexpr int value = 5;
+};
+
 // PM: attractor form compiled in (0 literal, 1 per unit mass); the host picks
 // the instance that matches the rates' per_mass flag.
 template <int Q, class ST, bool MASK, int PM, bool SPLIT>

@@ -137,13 +137,19 @@ inline int even_block(int nx, int most) {
 // Blocks of the adjoint launch: a multiple of 8 (one share per XCD), each block
 // visiting at most kAdjItems row segments (each thread that many nodes).
 constexpr uint64_t kAdjItems = 8;
-inline int adjoint_block(const Geom& g) { return even_block(g.nx, 256); }
 inline int adjoint_blocks(const Geom& g) {
-  const int bx = adjoint_block(g);
-  const uint64_t items = uint64_t((g.nx + bx - 1) / bx) * uint64_t(g.ny) * uint64_t(g.nz);
+  const uint64_t items = uint64_t((g.nx + 255) / 256) * uint64_t(g.ny) * uint64_t(g.nz);
   uint64_t nb = (items + kAdjItems - 1) / kAdjItems;
   nb = ((nb + 7) / 8) * 8;
   return int(nb);
+}
+// Segments of equal size where the stride of a block's items (its XCD's blocks) is
+// a multiple of a row's segments: a thread's chain of multiply-adds then stays in one
+// segment, and has the same nodes in it as with segments of 256.  Elsewhere it would
+// have others, and the gradients other roundings.
+inline int adjoint_block(const Geom& g) {
+  const int nseg = (g.nx + 255) / 256;
+  return nseg == 1 || adjoint_blocks(g) / 8 % nseg == 0 ? even_block(g.nx, 256) : 256;
 }
 
 // Whether the adjoint takes the form with a wavefront per row segment (k_adjoint's
@@ -163,7 +169,8 @@ inline int adjoint_rows(int q, bool wide, const Geom& g) {
 constexpr int kTotalsBlocks = 2048;
 constexpr int kReduceChunks = 256;
 
-// Blocks of one step launch (one block per CMLBM_STEP_BLOCK-wide row segment).
+// Blocks of one launch of the step with totals (one per segment of a row, at most
+// CMLBM_STEP_BLOCK nodes wide).
 uint64_t step_blocks(const Geom& g);
 
 // Static device scratch of the allocation-free fused-totals step: room for the

@@ -321,7 +321,7 @@ __device__ __forceinline__ void collide(R (&f)[Q], R Fx, R Fy, R Fz, const Rates
 // ---------------------------------------------------------------------------
 // The fused pull-stream + collide + force step
 // ---------------------------------------------------------------------------
-// Launch shape: one block covers CMLBM_STEP_BLOCK consecutive x of one row, so
+// Launch shape: one block covers up to CMLBM_STEP_BLOCK consecutive x of one row, so
 // every row base is uniform across the block.  Hardware hands consecutive
 // block ids to the eight XCDs in turn; with CMLBM_XCD_REMAP the block id is
 // permuted so that each XCD receives a contiguous run of rows, keeping a row's
