@@ -129,6 +129,28 @@ def build_host_math(verbose=False):
     return HOST_LIB
 
 
+PLAN_SRC = os.path.join(HOST_DIR, "host_plan.cpp")
+PLAN_LIB = os.path.join(HOST_DIR, "libhostplan.so")
+
+
+def build_host_plan(verbose=False):
+    """The library's launch rules (which lattices run in which form) as a shared
+    library for the tests (tests/host/host_plan.cpp includes the headers that
+    the launches use)."""
+    tmp = PLAN_LIB + ".tmp"
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    cmd = [_cxx(), *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__", "-isystem", os.path.join(rocm, "include"), "-O2", "-fPIC",
+           "-shared", PLAN_SRC, "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("building the host launch rules failed")
+    os.replace(tmp, PLAN_LIB)
+    return PLAN_LIB
+
+
 def build_host_sanitized(verbose=False):
     """The same host code as an executable with AddressSanitizer and
     UndefinedBehaviorSanitizer, driven by tests/host/sanitize_main.cpp (CPU only)."""
@@ -148,5 +170,6 @@ def build_host_sanitized(verbose=False):
 if __name__ == "__main__":
     print(build(verbose=True))
     print(build_host_math(verbose=True))
+    print(build_host_plan(verbose=True))
     print(build_c_test(verbose=True))
     print(build_probe(verbose=True))

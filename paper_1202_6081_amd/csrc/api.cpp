@@ -13,6 +13,7 @@
 
 #include "checks.hpp"
 #include "kernels.hpp"
+#include "step2_plan.hpp"
 
 struct cmlbm_sim {
   int q = 27;
@@ -312,9 +313,9 @@ cmlbm_status cmlbm_init_equilibrium_inplace(cmlbm_sim* s, const void* rho_dev, c
 namespace {
 
 // scratch: [step_blocks][4] partials followed by [kReduceChunks][4] stage sums
-// (used only with totals_dev).  steps: 1, or 2 (no totals) in one pass.
+// (used only with totals_dev).  two: the tiles of two steps (no totals) in one pass.
 cmlbm_status step_common(cmlbm_sim* s, const void* f_in, void* f_out, double* totals_dev, double* scratch,
-                         void* stream, int steps = 1) {
+                         void* stream, const cmlbm::Tiles2* two = nullptr) {
   if (!f_in || !f_out) return fail(s, CMLBM_EINVAL, "NULL population buffer");
   if (f_in == f_out) return fail(s, CMLBM_EINVAL, "f_in and f_out must differ (pull streaming)");
   CMLBM_CHECK_ALIGNED(s, {f_in, pop_bytes(s)}, {f_out, pop_bytes(s)}, {totals_dev, sizeof(double)});
@@ -348,7 +349,7 @@ cmlbm_status step_common(cmlbm_sim* s, const void* f_in, void* f_out, double* to
     a32.totals = totals_dev;
   }
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  if (steps == 2) return check_hip(s, cmlbm::launch_step2(s->q, s->prec, a64, a32, st), "step");
+  if (two) return check_hip(s, cmlbm::launch_step2(s->q, s->prec, a64, a32, *two, st), "step");
   return check_hip(s, cmlbm::launch_step(s->q, s->prec, a64, a32, st), "step");
 }
 
@@ -387,13 +388,14 @@ cmlbm_status cmlbm_run(cmlbm_sim* s, void* f_a, void* f_b, int nsteps, void* str
   // Pairs of steps in one pass where that pays, in even number and with a single
   // step last: the buffers change places as often as with single steps, modulo
   // two, and end up with the last two states.
-  const int pairs = nsteps > 0 && cmlbm::step2_pays(s->q, s->prec, s->g, s->mask != nullptr) ? (nsteps - 1) / 4 * 2 : 0;
+  cmlbm::Tiles2 tiles{};
+  const int pairs = nsteps > 4 && cmlbm::step2_plan(s->q, s->prec, s->g, s->mask != nullptr, tiles) ? (nsteps - 1) / 4 * 2 : 0;
   int cur = 0;
   for (int n = 0; n < nsteps; cur ^= 1) {
-    const int k = n < 2 * pairs ? 2 : 1;
-    cmlbm_status st = step_common(s, bufs[cur], bufs[cur ^ 1], nullptr, nullptr, stream, k);
+    const bool two = n < 2 * pairs;
+    cmlbm_status st = step_common(s, bufs[cur], bufs[cur ^ 1], nullptr, nullptr, stream, two ? &tiles : nullptr);
     if (st != CMLBM_OK) return st;
-    n += k;
+    n += two ? 2 : 1;
   }
   if (result_in_b) *result_in_b = nsteps & 1;
   return ok(s);

@@ -84,9 +84,9 @@ struct AdjArgs {
 // prec: 0 FP64, 1 FP32, 2 FP32 compute / FP16 deviation storage, 3 BF16 deviations.
 hipError_t launch_step(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, hipStream_t st);
 // Two steps from a.fin to a.fout in one pass (no totals), the same populations as
-// two launch_step calls; step2_pays: whether that is the faster way.
-bool step2_pays(int q, int prec, const Geom& g, bool walls);
-hipError_t launch_step2(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, hipStream_t st);
+// two launch_step calls, by the tiles that step2_plan (step2_plan.hpp) makes.
+hipError_t launch_step2(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, const Tiles2& t,
+                        hipStream_t st);
 hipError_t launch_gather(int q, int prec, const AuxArgs<double>& a64, const AuxArgs<float>& a32, hipStream_t st);
 // Population buffer (blocked layout) <-> full populations in compute type,
 // structure of arrays [Q][N]; to_soa selects the direction.

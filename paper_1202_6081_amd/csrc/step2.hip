@@ -43,6 +43,7 @@
 
 #include "kernels.hpp"
 #include "node.hpp"
+#include "step2_plan.hpp"
 
 namespace cmlbm {
 namespace {
@@ -75,7 +76,7 @@ constexpr int xy_slot(int a) {
 template <int Q, class ST, bool MASK>
 struct Tile2 {
   static constexpr bool wide = sizeof(typename ST::T) == 8;
-  static constexpr int rows = wide && (Q == 27 || MASK) ? 4 : 8;
+  static constexpr int rows = tile2_rows(Q, wide, MASK);
   static constexpr bool in_lds = wide;      // and the exchange plane once instead of twice
   static constexpr int threads = 64 * (rows + 3);
 };
@@ -348,31 +349,6 @@ __global__ __launch_bounds__((Tile2<Q, ST, MASK>::threads)) void k_step2(StepArg
   }
 }
 
-constexpr uint32_t kSlots = 256;      // blocks at work at a time: one on a CU
-
-// Rows of a tail tile beside main ones: each row is cache lines of its own in
-// every load, so that a tile of 130 rows of 2 nodes holds up the launch (130 x
-// 130 x 70 D3Q27 FP32, two steps: 160 us at 130 rows, 82 at 40, 81 at 24, 89 at 12;
-// one step at a time 109 us).
-constexpr uint32_t kTailRows = 24;
-
-// Planes per block.  A block's time is its planes and about three more (two
-// planes of halo, filling the pipeline), and the launch's that of a block times
-// the rounds of kSlots blocks.
-uint32_t run_length(uint32_t tiles, uint32_t nz) {
-  uint64_t best = ~uint64_t(0);
-  uint32_t arg = nz;
-  for (uint32_t zlen = nz; zlen >= 1; --zlen) {
-    const uint64_t blocks = uint64_t(tiles) * ((nz + zlen - 1) / zlen);
-    const uint64_t cost = (blocks + kSlots - 1) / kSlots * (zlen + 3);
-    if (cost < best) {
-      best = cost;
-      arg = zlen;
-    }
-  }
-  return arg;
-}
-
 template <int Q, class ST, bool MASK, bool FULL>
 void launch_tiles(const StepArgs<typename ST::R>& a, const Tiles2& t, dim3 grid, hipStream_t st) {
   const dim3 block(Tile2<Q, ST, MASK>::threads);
@@ -383,33 +359,8 @@ void launch_tiles(const StepArgs<typename ST::R>& a, const Tiles2& t, dim3 grid,
 }
 
 template <int Q, class ST, bool MASK>
-hipError_t step2_impl(const StepArgs<typename ST::R>& a, hipStream_t st) {
-  using Tile = Tile2<Q, ST, MASK>;
-  constexpr uint32_t ROWS = Tile::rows, plane = 66 * (ROWS + 2), waves = Tile::threads / 64;
-  const uint32_t nx = uint32_t(a.g.nx), ny = uint32_t(a.g.ny), nz = uint32_t(a.g.nz);
-  Tiles2 t{};
-  t.nbx = (nx + 63) / 64;
-  // A short last block of the rows takes more rows, packed over the threads,
-  // where that is less work: collisions of both steps by all wavefronts for
-  // tail_rows rows, against ROWS + 3 and ROWS by wavefront for ROWS rows.
-  const uint32_t len = nx & 63u;
-  if (len) {
-    uint32_t r = plane / (len + 2) - 2;
-    if (Tile::in_lds && r * len > ROWS * 64) r = ROWS * 64 / len;
-    if (t.nbx > 1 && r > kTailRows) r = kTailRows;
-    if (r > ny) r = ny;
-    const uint32_t busy = ((len + 2) * (r + 2) + 63) / 64;
-    if (2 * busy * ((ny + r - 1) / r) < (waves + ROWS) * ((ny + ROWS - 1) / ROWS)) {
-      t.nbx -= 1;
-      t.tail_rows = r;
-      t.tail = (ny + r - 1) / r;
-      t.tail_width = Divider::of(len + 2);
-    }
-  }
-  t.main = t.nbx * ((ny + ROWS - 1) / ROWS);
-  t.zlen = run_length(t.main + t.tail, nz);
-  t.bx = Divider::of(t.nbx);
-  t.all = Divider::of(t.main + t.tail);
+hipError_t step2_impl(const StepArgs<typename ST::R>& a, const Tiles2& t, hipStream_t st) {
+  const uint32_t len = uint32_t(a.g.nx) & 63u, nz = uint32_t(a.g.nz);
   const dim3 grid((t.main + t.tail) * ((nz + t.zlen - 1) / t.zlen));
   if (len == 0)
     launch_tiles<Q, ST, MASK, true>(a, t, grid, st);
@@ -420,33 +371,14 @@ hipError_t step2_impl(const StepArgs<typename ST::R>& a, hipStream_t st) {
 
 }  // namespace
 
-// Where two steps in one pass are the faster way: FP64 and FP32 storage (16-bit
-// storage is bound by the collisions, of which this way has more) on lattices
-// that give the 256 CUs a few planes each.  Below 2^18 nodes the planes of halo
-// weigh as much as the traffic saved: 64^3 takes 0.74-0.87 of the time of single
-// steps (0.88-0.92 with walls), 56^3 0.92-0.98 (1.03-1.13), 32^3 1.3-1.4; D3Q15 FP32
-// with walls, the lightest, 1.12 at 64^3, 1.02 at 64 x 96 x 64, 0.84 at 128 x 64 x 64.
-// Rows that fill their last block badly leave lanes of the single steps idle, but
-// not here: 0.71-0.89 at 56 x 200 x 200.  (Up to nx = 8 single steps take
-// nodes whatever their rows, and are as fast below 2^18 nodes: 0.93-1.12 at 8 x 200 x 200
-// and 3 x 200 x 200, two steps over one.)
-// (The kernel's offsets within a plane of population rows have 32 bits.)
-bool step2_pays(int q, int prec, const Geom& g, bool walls) {
-  if (prec > 1) return false;
-  if (uint64_t(g.nxy) * uint64_t(q) * (prec == 0 ? 8 : 4) >= (uint64_t(1) << 32)) return false;
-  const uint64_t lanes = uint64_t((g.nx + 63) / 64) * 64 * uint64_t(g.ny) * uint64_t(g.nz);
-  const bool light = q == 15 && prec == 1 && walls;
-  if (g.N >= (uint64_t(1) << (light ? 19 : 18))) return true;
-  return lanes >= (uint64_t(1) << 20) && g.nx > 8;
-}
-
-hipError_t launch_step2(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, hipStream_t st) {
+hipError_t launch_step2(int q, int prec, const StepArgs<double>& a64, const StepArgs<float>& a32, const Tiles2& t,
+                        hipStream_t st) {
   if (prec == 0) {
-    if (q == 27) return a64.mask ? step2_impl<27, StF64, true>(a64, st) : step2_impl<27, StF64, false>(a64, st);
-    return a64.mask ? step2_impl<15, StF64, true>(a64, st) : step2_impl<15, StF64, false>(a64, st);
+    if (q == 27) return a64.mask ? step2_impl<27, StF64, true>(a64, t, st) : step2_impl<27, StF64, false>(a64, t, st);
+    return a64.mask ? step2_impl<15, StF64, true>(a64, t, st) : step2_impl<15, StF64, false>(a64, t, st);
   }
-  if (q == 27) return a32.mask ? step2_impl<27, StF32, true>(a32, st) : step2_impl<27, StF32, false>(a32, st);
-  return a32.mask ? step2_impl<15, StF32, true>(a32, st) : step2_impl<15, StF32, false>(a32, st);
+  if (q == 27) return a32.mask ? step2_impl<27, StF32, true>(a32, t, st) : step2_impl<27, StF32, false>(a32, t, st);
+  return a32.mask ? step2_impl<15, StF32, true>(a32, t, st) : step2_impl<15, StF32, false>(a32, t, st);
 }
 
 }  // namespace cmlbm

@@ -1,0 +1,48 @@
+"""Where cmlbm_run takes two steps in one pass over the populations (host rule).
+
+A block of that pass walks a tile of 64 nodes by 8 (or 4) rows along z and
+collides its halo too, so that lattices of a few rows or planes, or of few tiles
+and many planes, take longer than in single steps: the rule has to leave those
+alone, and to take the lattices that fill the tiles.
+"""
+import pytest
+
+from plan_helpers import step2_plan
+
+F64, F32, F16DEV, BF16DEV = 0, 1, 2, 3
+
+# (nx, ny, nz) that took 1.2 to 9 times as long as single steps
+FLAT = [(512, 515, 1), (2048, 2048, 1), (8192, 512, 1), (100, 2700, 1), (9, 30000, 1),
+        (512, 1, 515), (2048, 1, 2048), (64, 1, 4096), (100, 1, 2700), (9, 1, 30000),
+        (4, 4, 16384), (8, 8, 8192), (8, 8, 65535), (9, 4, 30000)]
+# ... and that gain in every kind
+ROOMY = [(256, 128, 16), (256, 256, 8), (512, 512, 4), (256, 8, 256), (512, 4, 512), (40, 200, 200), (24, 200, 200),
+         (9, 400, 400), (12, 300, 300), (128, 128, 128), (201, 131, 67), (384, 300, 300), (512, 512, 512)]
+
+
+@pytest.mark.parametrize("walls", [0, 1])
+@pytest.mark.parametrize("prec", [F64, F32])
+@pytest.mark.parametrize("q", [27, 15])
+def test_thin_lattices_keep_single_steps(q, prec, walls):
+    for nx, ny, nz in FLAT:
+        assert not step2_plan(q, prec, (nz, ny, nx), walls).pays, (nx, ny, nz)
+
+
+@pytest.mark.parametrize("walls", [0, 1])
+@pytest.mark.parametrize("prec", [F64, F32])
+@pytest.mark.parametrize("q", [27, 15])
+def test_lattices_that_fill_the_tiles_take_two_steps(q, prec, walls):
+    for nx, ny, nz in ROOMY:
+        assert step2_plan(q, prec, (nz, ny, nx), walls).pays, (nx, ny, nz)
+
+
+@pytest.mark.parametrize("q", [27, 15])
+def test_limits(q):
+    for prec in (F16DEV, BF16DEV):
+        assert not step2_plan(q, prec, (512, 512, 512), 0).pays
+    for prec in (F64, F32):
+        assert not step2_plan(q, prec, (56, 56, 56), 0).pays
+        # offsets inside a plane of population rows have 32 bits
+        ny = (2**32 // (8 if prec == F64 else 4) // q - 1) // 4096
+        assert step2_plan(q, prec, (8, ny, 4096), 0).pays
+        assert not step2_plan(q, prec, (8, ny + 1, 4096), 0).pays
