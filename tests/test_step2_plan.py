@@ -5,9 +5,11 @@ collides its halo too, so that lattices of a few rows or planes, or of few tiles
 and many planes, take longer than in single steps: the rule has to leave those
 alone, and to take the lattices that fill the tiles.
 """
+import timeit
+
 import pytest
 
-from plan_helpers import step2_plan
+from plan_helpers import lib, step2_plan
 
 F64, F32, F16DEV, BF16DEV = 0, 1, 2, 3
 
@@ -46,3 +48,21 @@ def test_limits(q):
         ny = (2**32 // (8 if prec == F64 else 4) // q - 1) // 4096
         assert step2_plan(q, prec, (8, ny, 4096), 0).pays
         assert not step2_plan(q, prec, (8, ny + 1, 4096), 0).pays
+
+
+def _planes_per_block(tiles, nz):
+    """Every plane count tried: rounds of 256 blocks, each its planes and three more."""
+    return min(range(nz, 0, -1), key=lambda z: -(-tiles * -(-nz // z) // 256) * (z + 3))
+
+
+def test_planes_per_block_are_the_best_of_all():
+    for tiles in [*range(1, 30), 64, 100, 127, 128, 129, 200, 255, 256, 257, 300, 511, 512, 1000, 4096, 70000]:
+        for nz in [*range(1, 20), 64, 67, 100, 255, 256, 257, 600, 1021]:
+            assert lib().hp_run_length(tiles, nz) == _planes_per_block(tiles, nz), (tiles, nz)
+
+
+def test_planes_per_block_take_no_time_on_tall_lattices():
+    # cmlbm_run asks once per call, where a step takes 5 us at least
+    for tiles in (1, 2, 7, 100, 129, 200, 255, 256, 300, 1000):
+        best = min(timeit.repeat(lambda: lib().hp_run_length(tiles, 65535), number=20, repeat=5)) / 20
+        assert best < 20e-6, (tiles, best)
