@@ -20,6 +20,11 @@ FLAT = [(512, 515, 1), (2048, 2048, 1), (8192, 512, 1), (100, 2700, 1), (9, 3000
 # ... and that gain in every kind
 ROOMY = [(256, 128, 16), (256, 256, 8), (512, 512, 4), (256, 8, 256), (512, 4, 512), (40, 200, 200), (24, 200, 200),
          (9, 400, 400), (12, 300, 300), (128, 128, 128), (201, 131, 67), (384, 300, 300), (512, 512, 512)]
+# (nz, ny, nx) that the GPU tests run, in every kind and in those that gain
+REACHED = [(500, 601, 2), (300, 258, 7), (512, 4, 512), (520, 4, 1000), (260, 63, 63), (67, 66, 128), (80, 67, 100),
+           (530, 8, 257), (200, 191, 65), (90, 130, 130), (200, 91, 33)]
+REACHED_BY_SOME = [(1025, 520, 1), (700, 701, 1), (170, 150, 10), (140, 130, 11), (130, 127, 15), (600, 3, 1100),
+                   (600, 2, 2000), (3, 700, 512), (2000, 17, 19), (64, 64, 64)]
 
 
 @pytest.mark.parametrize("walls", [0, 1])
@@ -66,3 +71,16 @@ def test_planes_per_block_take_no_time_on_tall_lattices():
     for tiles in (1, 2, 7, 100, 129, 200, 255, 256, 300, 1000):
         best = min(timeit.repeat(lambda: lib().hp_run_length(tiles, 65535), number=20, repeat=5)) / 20
         assert best < 20e-6, (tiles, best)
+
+
+def test_the_lattices_of_the_gpu_tests_are_reached():
+    kinds = [(q, prec, walls) for q in (27, 15) for prec in (F64, F32) for walls in (0, 1)]
+    for shape in REACHED:
+        assert all(step2_plan(q, prec, shape, walls).pays for q, prec, walls in kinds), shape
+    for shape in REACHED_BY_SOME:
+        assert any(step2_plan(q, prec, shape, walls).pays for q, prec, walls in kinds), shape
+    for q, prec, walls in kinds:
+        some = [s for s in REACHED_BY_SOME if step2_plan(q, prec, s, walls).pays]
+        assert len(some) >= 2, (q, prec, walls)
+        tiles = [step2_plan(q, prec, s, walls) for s in REACHED + some]
+        assert any(t.main and t.tail for t in tiles) and any(not t.main for t in tiles) and any(not t.tail for t in tiles)
