@@ -1347,19 +1347,6 @@ inline RowMap row_map(const Geom& g, int bx) {
   return {nseg, Divider::of(nseg), Divider::of(uint32_t(g.ny))};
 }
 
-// Whether k_step_thin takes a step.  Measured against the row kernel (as a ratio of
-// its time, both lattices and all storage types, without and with walls): nx <= 8
-// wins from about 1600 rows (0.53 to 1.02; 1.3 at 135 rows, where a step is all latency),
-// nx = 12 and 16 from 4096 (0.65 to 1.02; 1.3 at 1024), nx = 24 and 32 only with
-// 40000 rows and for 16-bit storage (0.65 to 0.97; at 10000 rows up to 1.18),
-// where the wider types are at the memory's rate (1.03 at 32 x 400 x 400) and a
-// run takes two steps per pass.  From nx = 40 the row kernel is ahead.
-inline bool thin_pays(const Geom& g, bool narrow) {
-  if (g.nx > 32 || g.N >= (int64_t(1) << 31)) return false;
-  const int64_t rows = int64_t(g.ny) * g.nz;
-  return rows >= (g.nx <= 8 ? 1536 : g.nx <= 16 ? 4096 : 16384) && (g.nx <= 16 || narrow);
-}
-
 // The block partials of a step's totals summed into args.totals: in one launch
 // while a thread has few rows, else in two stages.  (Four steps of 32^3 FP64 with
 // totals, 1024 rows of partials: 77.7 -> 65.7 us.)
@@ -1380,7 +1367,7 @@ hipError_t step_impl(const StepArgs<typename ST::R>& args, hipStream_t st) {
   const dim3 grid = step_grid(args.g, bx);
   StepArgs<typename ST::R> a = args;
   a.rm = row_map(a.g, bx);
-  if (!a.partials && thin_pays(a.g, sizeof(typename ST::T) == 2)) {
+  if (!a.partials && thin_pays(Q, int(sizeof(typename ST::T)), a.mask != nullptr, a.g)) {
     a.rm = {uint32_t(a.g.nx), Divider::of(uint32_t(a.g.nx)), Divider::of(uint32_t(a.g.ny))};
     const dim3 blocks(unsigned((a.g.N + 63) / 64));
     if (a.mask)

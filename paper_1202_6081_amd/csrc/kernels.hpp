@@ -125,6 +125,31 @@ hipError_t launch_init_adjoint(int q, int prec, const Geom& g, const void* u0, c
                                const uint8_t* mask, const ForceArgs<double>& f64, const ForceArgs<float>& f32,
                                double* dLdF, double* partials, int nblk, hipStream_t st);
 
+// Whether a step takes the nodes in a row, whatever rows of the lattice they are in
+// (k_step_thin), by the bytes of a stored population.  Measured against the row kernel,
+// as a ratio of its time:
+//   * nx <= 8, every kind: 0.53 to 1.01 from 1296 rows (1.3 at 135 rows, where a step is
+//     all latency);
+//   * nx = 9 to 16, where a row is a large part of a wavefront: with walls 0.52 to 1.08
+//     from 4096 rows; without, D3Q27 FP64 0.49 to 1.00 from there, but FP32 0.90 to 1.24
+//     at 4970 rows and 0.95 to 1.11 at 7140, 0.73 to 0.95 at 10920, D3Q15 FP32 0.72 to 1.21
+//     at 9506, 0.73 to 0.99 at 19740; D3Q27 16-bit 0.82 to 1.08 up to 7140, 0.73 to 0.98
+//     from 8190; D3Q15 16-bit 0.63 to 1.08, D3Q15 FP64 0.72 to 1.12 up to 7140, 0.52 to
+//     0.98 from 8190;
+//   * nx = 17 to 32, 16-bit storage: 0.74 to 1.14 at 8100 to 12100 rows, 0.50 to 1.06
+//     from 16384.  (The wider types are at the memory's rate in rows: 1.03 at 32 x
+//     400 x 400, and a run takes two steps per pass.)
+// From nx = 40 the row kernel is ahead.
+inline bool thin_pays(int q, int bytes, bool walls, const Geom& g) {
+  if (g.nx > 32 || g.N >= (uint64_t(1) << 31)) return false;
+  const uint64_t rows = uint64_t(g.ny) * uint64_t(g.nz);
+  if (g.nx <= 8) return rows >= 1536;
+  if (g.nx > 16) return bytes == 2 && rows >= 16384;
+  if (walls) return rows >= 4096;
+  if (bytes == 4) return rows >= (q == 27 ? 10240 : 16384);
+  return rows >= ((q == 27) == (bytes == 8) ? 4096 : 8192);
+}
+
 // Threads of a block that takes segments of rows of nx nodes, at most `most`: as
 // few segments as blocks of `most` give, of about the same number of wavefronts (nx
 // = 320: 192 + 128, not 256 + 64 with three of eight wavefronts idle).  The adjoint

@@ -1,5 +1,6 @@
 // Host build of the library's launch rules, for the tests: which lattices take
-// two steps in one pass and by what tiles, and the adjoint's launch form.
+// two steps in one pass and by what tiles, which take their nodes in a row, and the
+// adjoint's launch form.
 #include <cstdint>
 
 #include "step2_plan.hpp"
@@ -33,6 +34,11 @@ int hp_step2_plan(int q, int prec, int nx, int ny, int nz, int walls, uint32_t* 
 }
 
 uint32_t hp_run_length(uint32_t tiles, uint32_t nz) { return cmlbm::run_length(tiles, nz); }
+
+// Whether a step without totals takes the nodes in a row.
+int hp_thin(int q, int bytes, int nx, int ny, int nz, int walls) {
+  return cmlbm::thin_pays(q, bytes, walls != 0, geom(nx, ny, nz)) ? 1 : 0;
+}
 
 // The adjoint step's launch; out: blocks, nodes of a row segment, 1 in the form
 // with a wavefront per segment.

@@ -34,3 +34,8 @@ def adjoint_launch(q, prec, shape):
     out = (ctypes.c_int * 3)()
     lib().hp_adjoint(q, prec, nx, ny, nz, out)
     return Adjoint(out[0], out[1], bool(out[2]))
+
+
+def thin_pays(q, prec, shape, walls):
+    nz, ny, nx = shape
+    return bool(lib().hp_thin(q, (8, 4, 2, 2)[prec], nx, ny, nz, int(walls)))
