@@ -1278,10 +1278,12 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Rows of block partials that one block per column sums by itself: 32 loads a
-// thread at most.  (The two stages take 11.5 + 4.7 us for the adjoint's 26 columns and
-// 3.7 + 2.0 for a step's four at any small number.)
-constexpr uint64_t kOneStageRows = 8192;
+// Rows of block partials that one block per column sums by itself, in one launch; more
+// go in two stages.  One launch against two, in us: a step's four columns -2.5 at 256
+// to 1024 rows, -1.3 at 2500, +0.6 at 4096, +4.6 at 8100 (of a step of 15); the
+// adjoint's 26, of which a load takes 8 in 208 bytes, -10 at 1024, -5.5 at 4050, -0.2 at
+// 6050, +4.3 at 8160.
+constexpr uint64_t kOneStageTotals = 3584, kOneStageAdjoint = 6144;
 
 // Threads of a step's block where its number of blocks matters: a row of partial
 // totals each.
@@ -1348,12 +1350,12 @@ inline RowMap row_map(const Geom& g, int bx) {
 }
 
 // The block partials of a step's totals summed into args.totals: in one launch
-// while a thread has few rows, else in two stages.  (Four steps of 32^3 FP64 with
+// while there are few rows, else in two stages.  (Four steps of 32^3 FP64 with
 // totals, 1024 rows of partials: 77.7 -> 65.7 us.)
 template <typename R>
 void sum_totals(const StepArgs<R>& a, uint64_t rows, hipStream_t st) {
   const double* from = a.partials;
-  if (rows > kOneStageRows) {
+  if (rows > kOneStageTotals) {
     hipLaunchKernelGGL(k_reduce_chunks<4>, dim3(kReduceChunks), dim3(kBlock), 0, st, a.partials, rows, a.stage);
     from = a.stage;
     rows = kReduceChunks;
@@ -1518,7 +1520,7 @@ hipError_t adjoint_impl(const AdjArgs<typename ST::R>& a, double* partials, int 
   // runs of rows (all 26 columns), then one block per column the chunk sums.
   const double* rows = partials;
   int nrows = adjoint_rows(Q, sizeof(typename ST::R) == 8, a.g);
-  if (uint64_t(nrows) > kOneStageRows) {
+  if (uint64_t(nrows) > kOneStageAdjoint) {
     double* stage = partials + uint64_t(26) * uint64_t(nrows);
     hipLaunchKernelGGL(k_reduce_chunks<26>, dim3(kReduceChunks), dim3(kBlock), 0, st, partials, uint64_t(nrows), stage);
     rows = stage;
