@@ -263,6 +263,7 @@ CMLBM_HD void populations_from_central15(R (&m)[15], R ux, R uy, R uz, R (&f)[15
 // Density and velocity (Eqs. densitycalculation, velocitycalculation).
 template <typename R>
 CMLBM_HD void moments0_15(const R (&f)[15], R Fx, R Fy, R Fz, R& rho, R& ux, R& uy, R& uz, R& inv_rho) {
+  CMLBM_FMA_AS_WRITTEN
   rho = R(0);
 #pragma unroll
   for (int a = 0; a < 15; ++a) rho += f[a];
@@ -275,9 +276,9 @@ CMLBM_HD void moments0_15(const R (&f)[15], R Fx, R Fy, R Fz, R& rho, R& ux, R& 
   }
   const R inv = recip(rho);
   inv_rho = inv;
-  ux = (f[1] - f[2] + cx + R(0.5) * Fx) * inv;
-  uy = (f[3] - f[4] + cy + R(0.5) * Fy) * inv;
-  uz = (f[5] - f[6] + cz + R(0.5) * Fz) * inv;
+  ux = fma_r(R(0.5), Fx, f[1] - f[2] + cx) * inv;
+  uy = fma_r(R(0.5), Fy, f[3] - f[4] + cy) * inv;
+  uz = fma_r(R(0.5), Fz, f[5] - f[6] + cz) * inv;
 }
 
 // Raw moments of the source S = K D^-1 m^s (Appendix G), in the moment order
@@ -285,60 +286,73 @@ CMLBM_HD void moments0_15(const R (&f)[15], R Fx, R Fy, R Fz, R& rho, R& ux, R& 
 // they follow from the printed projections m^s alone: e.g. the xx moment is
 // m^s_7/2 + m^s_8/6 + m^s_9/3 = 2 F_x u_x and the xyy moment is
 // (4/5) m^s_1 + m^s_10/10.
+// Added to the raw moments m.
 template <typename R>
-CMLBM_HD void source_raw15(R Fx, R Fy, R Fz, R ux, R uy, R uz, R (&r)[15]) {
+CMLBM_HD void add_source_raw15(R Fx, R Fy, R Fz, R ux, R uy, R uz, R (&m)[15]) {
+  CMLBM_FMA_AS_WRITTEN
   const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
   const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
-  r[0] = R(0);
-  r[1] = Fx;
-  r[2] = Fy;
-  r[3] = Fz;
-  r[4] = Fx * uy + Fy * ux;
-  r[5] = Fx * uz + Fz * ux;
-  r[6] = Fy * uz + Fz * uy;
-  r[7] = R(2) * Fu;
-  r[8] = R(2) * Fv;
-  r[9] = R(2) * Fw;
-  r[10] = R(0.5) * (Fx * (R(3) * ux2 + uy2 + uz2 - R(1)) + R(2) * ux * (Fv + Fw));
-  r[11] = R(0.5) * (Fy * (ux2 + R(3) * uy2 + uz2 - R(1)) + R(2) * uy * (Fu + Fw));
-  r[12] = R(0.5) * (Fz * (ux2 + uy2 + R(3) * uz2 - R(1)) + R(2) * uz * (Fu + Fv));
-  r[13] = Fx * uy * uz + Fy * ux * uz + Fz * ux * uy;
-  r[14] = R(2.0 / 3.0) * (Fu * (uy2 + uz2) + Fv * (ux2 + uz2) + Fw * (ux2 + uy2));
+  const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
+  m[MX] += Fx;
+  m[MY] += Fy;
+  m[MZ] += Fz;
+  m[MXY] += fma_r(Fx, uy, Fy * ux);
+  m[MXZ] += fma_r(Fx, uz, Fz * ux);
+  m[MYZ] += fma_r(Fz, uy, Fy * uz);
+  m[MXX] = fma_r(R(2), Fu, m[MXX]);
+  m[MYY] = fma_r(R(2), Fv, m[MYY]);
+  m[MZZ] = fma_r(R(2), Fw, m[MZZ]);
+  const R cx = fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1), cy = fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1);
+  const R cz = fma_r(R(3), uz2, xy2) - R(1);
+  m[MXYY] = fma_r(R(0.5), fma_r(ux + ux, fma_r(Fy, uy, Fw), Fx * cx), m[MXYY]);
+  m[MXXY] = fma_r(R(0.5), fma_r(uy + uy, fma_r(Fx, ux, Fw), Fy * cy), m[MXXY]);
+  m[MXXZ] = fma_r(R(0.5), fma_r(uz + uz, fma_r(Fy, uy, Fu), Fz * cz), m[MXXZ]);
+  m[MXYZ] += fma_r(uy, Fz * ux, fma_r(uz, Fx * uy, uz * (Fy * ux)));
+  m[MXXYY] = fma_r(R(2.0 / 3.0), fma_r(Fw, xy2, fma_r(Fu, yz2, Fv * xz2)), m[MXXYY]);
 }
 
-// Adjoint of source_raw15 with respect to F and u (gr: adjoint of r).
+// Adjoint of add_source_raw15 with respect to F and u (gr: adjoint of m).
 template <typename R>
 CMLBM_HD void source_raw15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gr)[15], R& gFx, R& gFy, R& gFz,
                                R& gux, R& guy, R& guz) {
+  CMLBM_FMA_AS_WRITTEN
   const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
   const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
-  gFx += gr[1] + uy * gr[4] + uz * gr[5] + R(2) * ux * gr[7];
-  gFy += gr[2] + ux * gr[4] + uz * gr[6] + R(2) * uy * gr[8];
-  gFz += gr[3] + ux * gr[5] + uy * gr[6] + R(2) * uz * gr[9];
-  gux += Fy * gr[4] + Fz * gr[5] + R(2) * Fx * gr[7];
-  guy += Fx * gr[4] + Fz * gr[6] + R(2) * Fy * gr[8];
-  guz += Fx * gr[5] + Fy * gr[6] + R(2) * Fz * gr[9];
+  const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
+  const R x2 = R(2) * ux, y2 = R(2) * uy, z2 = R(2) * uz;
+  gFx += fma_r(x2, gr[7], fma_r(uz, gr[5], fma_r(uy, gr[4], gr[1])));
+  gFy += fma_r(y2, gr[8], fma_r(uz, gr[6], fma_r(ux, gr[4], gr[2])));
+  gFz += fma_r(z2, gr[9], fma_r(uy, gr[6], fma_r(ux, gr[5], gr[3])));
+  gux += fma_r(R(2) * Fx, gr[7], fma_r(Fz, gr[5], Fy * gr[4]));
+  guy += fma_r(R(2) * Fy, gr[8], fma_r(Fz, gr[6], Fx * gr[4]));
+  guz += fma_r(R(2) * Fz, gr[9], fma_r(Fy, gr[6], Fx * gr[5]));
   // third order
-  gFx += R(0.5) * (R(3) * ux2 + uy2 + uz2 - R(1)) * gr[10] + ux * uy * gr[11] + ux * uz * gr[12];
-  gFy += ux * uy * gr[10] + R(0.5) * (ux2 + R(3) * uy2 + uz2 - R(1)) * gr[11] + uy * uz * gr[12];
-  gFz += ux * uz * gr[10] + uy * uz * gr[11] + R(0.5) * (ux2 + uy2 + R(3) * uz2 - R(1)) * gr[12];
-  gux += (R(3) * Fu + Fv + Fw) * gr[10] + (Fy * ux + Fx * uy) * gr[11] + (Fz * ux + Fx * uz) * gr[12];
-  guy += (Fx * uy + Fy * ux) * gr[10] + (R(3) * Fv + Fu + Fw) * gr[11] + (Fz * uy + Fy * uz) * gr[12];
-  guz += (Fx * uz + Fz * ux) * gr[10] + (Fy * uz + Fz * uy) * gr[11] + (R(3) * Fw + Fu + Fv) * gr[12];
-  gFx += uy * uz * gr[13];
-  gFy += ux * uz * gr[13];
-  gFz += ux * uy * gr[13];
-  gux += (Fy * uz + Fz * uy) * gr[13];
-  guy += (Fx * uz + Fz * ux) * gr[13];
-  guz += (Fx * uy + Fy * ux) * gr[13];
+  const R cx = R(0.5) * (fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1));
+  const R cy = R(0.5) * (fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1));
+  const R cz = R(0.5) * (fma_r(R(3), uz2, xy2) - R(1));
+  const R uxy = ux * uy, uxz = ux * uz, uyz = uy * uz;
+  gFx += fma_r(uxz, gr[12], fma_r(cx, gr[10], uxy * gr[11]));
+  gFy += fma_r(uyz, gr[12], fma_r(uxy, gr[10], cy * gr[11]));
+  gFz += fma_r(cz, gr[12], fma_r(uxz, gr[10], uyz * gr[11]));
+  const R Fvw = Fv + Fw, Fuw = Fu + Fw, Fuv = Fu + Fv;
+  const R Fxy = fma_r(Fx, uy, Fy * ux), Fxz = fma_r(Fx, uz, Fz * ux), Fyz = fma_r(Fy, uz, Fz * uy);
+  gux += fma_r(Fxz, gr[12], fma_r(fma_r(R(3), Fu, Fvw), gr[10], Fxy * gr[11]));
+  guy += fma_r(Fyz, gr[12], fma_r(Fxy, gr[10], fma_r(R(3), Fv, Fuw) * gr[11]));
+  guz += fma_r(fma_r(R(3), Fw, Fuv), gr[12], fma_r(Fxz, gr[10], Fyz * gr[11]));
+  gFx = fma_r(uyz, gr[13], gFx);
+  gFy = fma_r(uxz, gr[13], gFy);
+  gFz = fma_r(uxy, gr[13], gFz);
+  gux = fma_r(Fyz, gr[13], gux);
+  guy = fma_r(Fxz, gr[13], guy);
+  guz = fma_r(Fxy, gr[13], guz);
   // fourth order
   const R c = R(2.0 / 3.0) * gr[14];
-  gFx += c * ux * (uy2 + uz2);
-  gFy += c * uy * (ux2 + uz2);
-  gFz += c * uz * (ux2 + uy2);
-  gux += c * (Fx * (uy2 + uz2) + R(2) * ux * (Fv + Fw));
-  guy += c * (Fy * (ux2 + uz2) + R(2) * uy * (Fu + Fw));
-  guz += c * (Fz * (ux2 + uy2) + R(2) * uz * (Fu + Fv));
+  gFx = fma_r(c * ux, yz2, gFx);
+  gFy = fma_r(c * uy, xz2, gFy);
+  gFz = fma_r(c * uz, xy2, gFz);
+  gux = fma_r(c, fma_r(Fx, yz2, x2 * Fvw), gux);
+  guy = fma_r(c, fma_r(Fy, xz2, y2 * Fuw), guy);
+  guz = fma_r(c, fma_r(Fz, xy2, z2 * Fuv), guz);
 }
 
 // shift15 with its multiply-adds as written.
@@ -370,28 +384,8 @@ CMLBM_HD void collide15(R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& p) {
   const R ux = fma_r(R(0.5), Fx, m[MX]) * inv_rho;
   const R uy = fma_r(R(0.5), Fy, m[MY]) * inv_rho;
   const R uz = fma_r(R(0.5), Fz, m[MZ]) * inv_rho;
-  // raw moments of h = f + S (source_raw15), then central moments about u
-  {
-    const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
-    const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
-    const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
-    m[MX] += Fx;
-    m[MY] += Fy;
-    m[MZ] += Fz;
-    m[MXY] += fma_r(Fx, uy, Fy * ux);
-    m[MXZ] += fma_r(Fx, uz, Fz * ux);
-    m[MYZ] += fma_r(Fz, uy, Fy * uz);
-    m[MXX] = fma_r(R(2), Fu, m[MXX]);
-    m[MYY] = fma_r(R(2), Fv, m[MYY]);
-    m[MZZ] = fma_r(R(2), Fw, m[MZZ]);
-    const R cx = fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1), cy = fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1);
-    const R cz = fma_r(R(3), uz2, xy2) - R(1);
-    m[MXYY] = fma_r(R(0.5), fma_r(ux + ux, fma_r(Fy, uy, Fw), Fx * cx), m[MXYY]);
-    m[MXXY] = fma_r(R(0.5), fma_r(uy + uy, fma_r(Fx, ux, Fw), Fy * cy), m[MXXY]);
-    m[MXXZ] = fma_r(R(0.5), fma_r(uz + uz, fma_r(Fy, uy, Fu), Fz * cz), m[MXXZ]);
-    m[MXYZ] += fma_r(uy, Fz * ux, fma_r(uz, Fx * uy, uz * (Fy * ux)));
-    m[MXXYY] = fma_r(R(2.0 / 3.0), fma_r(Fw, xy2, fma_r(Fu, yz2, Fv * xz2)), m[MXXYY]);
-  }
+  // raw moments of h = f + S, then central moments about u
+  add_source_raw15(Fx, Fy, Fz, ux, uy, uz, m);
   shift15_as_written<0>(m, -ux);
   shift15_as_written<1>(m, -uy);
   shift15_as_written<2>(m, -uz);
@@ -460,22 +454,25 @@ CMLBM_HD void initial15(R rho, R ux, R uy, R uz, R Fx, R Fy, R Fz, R (&f)[15]) {
 // adjoint of its input); adds d/du to gu.
 template <int AX, typename R>
 CMLBM_HD void shift15_adj(const R (&m)[15], R u, R sg, R (&g)[15], R& gu) {
+  CMLBM_FMA_AS_WRITTEN
   constexpr Groups15 G = groups15<AX>();
   const R v = sg * u;
   R gv = R(0);
   static_for<G.nt>([&](auto i) {
+    CMLBM_FMA_AS_WRITTEN
     constexpr int a = G.t[decltype(i)::value][0], b = G.t[decltype(i)::value][1], c = G.t[decltype(i)::value][2];
     const R g1 = g[b], g2 = g[c];
-    gv += g1 * m[a] + g2 * R(2) * (m[b] + v * m[a]);
-    g[a] += v * g1 + v * v * g2;
-    g[b] = g1 + R(2) * v * g2;
+    gv += fma_r(g1, m[a], R(2) * g2 * fma_r(v, m[a], m[b]));
+    g[a] += fma_r(v, g1, v * v * g2);
+    g[b] = fma_r(R(2) * v, g2, g1);
   });
   static_for<G.np>([&](auto i) {
+    CMLBM_FMA_AS_WRITTEN
     constexpr int a = G.p[decltype(i)::value][0], b = G.p[decltype(i)::value][1];
-    gv += g[b] * m[a];
-    g[a] += v * g[b];
+    gv = fma_r(g[b], m[a], gv);
+    g[a] = fma_r(v, g[b], g[a]);
   });
-  gu += sg * gv;
+  gu = fma_r(sg, gv, gu);
 }
 
 // Raw moments of h, and the transpose (adjoint) of that linear map.
@@ -509,6 +506,7 @@ CMLBM_HD void raw15_adj(const R (&gr)[15], R (&gh)[15]) {
 // gs = (d f / d s)^T g.
 template <typename R>
 CMLBM_HD void inverse15_adj(const R (&g)[15], R (&gs)[15]) {
+  CMLBM_FMA_AS_WRITTEN
   R c = R(0), cx = R(0), cy = R(0), cz = R(0), cxy = R(0), cxz = R(0), cyz = R(0), cxyz = R(0);
 #pragma unroll
   for (int a = 7; a < 15; ++a) {
@@ -535,11 +533,11 @@ CMLBM_HD void inverse15_adj(const R (&g)[15], R (&gs)[15]) {
   gs[7] = p1 - g[0];
   gs[8] = p2 - g[0];
   gs[9] = p3 - g[0];
-  gs[10] = R(0.125) * cx - m1;
-  gs[11] = R(0.125) * cy - m2;
-  gs[12] = R(0.125) * cz - m3;
+  gs[10] = fma_r(R(0.125), cx, -m1);
+  gs[11] = fma_r(R(0.125), cy, -m2);
+  gs[12] = fma_r(R(0.125), cz, -m3);
   gs[13] = R(0.125) * cxyz;
-  gs[14] = R(0.125) * c - (p1 + p2 + p3) + R(2) * g[0];
+  gs[14] = fma_r(R(2), g[0], fma_r(R(0.125), c, -(p1 + p2 + p3)));
 }
 
 // Adjoint of source15 with respect to F and u: gS = adjoint of S.
@@ -608,6 +606,7 @@ CMLBM_HD void source15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gS)[15]
 template <int PM = -1, typename R, typename W>
 CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& p, R (&g)[15], R& gFx, R& gFy,
                             R& gFz, W& gw) {
+  CMLBM_FMA_AS_WRITTEN
   const bool pm = PM < 0 ? p.per_mass != 0 : PM != 0;
   R rho, ux, uy, uz, inv_rho;
   moments0_15(f, Fx, Fy, Fz, rho, ux, uy, uz, inv_rho);
@@ -616,23 +615,19 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
 
   // forward: central moments c of h = f + S (raw moments of f plus those of S)
   R c[15];
-  {
-    R rs[15];
-    raw15(f, c);
-    source_raw15(Fx, Fy, Fz, ux, uy, uz, rs);
-#pragma unroll
-    for (int m = 0; m < 15; ++m) c[m] += rs[m];
-  }
-  shift15<0>(c, ux, R(-1));
-  shift15<1>(c, uy, R(-1));
-  shift15<2>(c, uz, R(-1));
+  raw15(f, c);
+  add_source_raw15(Fx, Fy, Fz, ux, uy, uz, c);
+  shift15_as_written<0>(c, -ux);
+  shift15_as_written<1>(c, -uy);
+  shift15_as_written<2>(c, -uz);
   // relaxed central moments t (conserved rows: rho and F/2)
-  const R d1 = p.wc[7] * (c[7] - c[8]);
-  const R d2 = p.wc[8] * (c[7] + c[8] - R(2) * c[9]);
-  const R t9 = p.wc[9] * (c[7] + c[8] + c[9]) + p.w[9] * rho;
-  const R txx = (R(2) * t9 + d2 + R(3) * d1) * R(1.0 / 6.0);
-  const R tyy = (R(2) * t9 + d2 - R(3) * d1) * R(1.0 / 6.0);
-  const R tzz = (t9 - d2) * R(1.0 / 3.0);
+  const R D1 = c[7] - c[8], xy2 = c[7] + c[8], D2 = fma_r(R(-2), c[9], xy2), T = xy2 + c[9];
+  const R d1 = p.wc[7] * D1;
+  const R t9 = fma_r(p.w[9], rho, p.wc[9] * T);
+  const R td = fma_r(p.wc[8], D2, t9 + t9);
+  const R txx = fma_r(d1, R(3), td) * R(1.0 / 6.0);
+  const R tyy = fma_r(d1, R(-3), td) * R(1.0 / 6.0);
+  const R tzz = fma_r(-p.wc[8], D2, t9) * R(1.0 / 3.0);
   R t[15];
   t[0] = rho;
   t[1] = R(0.5) * Fx;
@@ -645,7 +640,7 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
   t[9] = tzz;
 #pragma unroll
   for (int m = 10; m < 14; ++m) t[m] = p.wc[m] * c[m];
-  t[14] = p.wc[14] * c[14] + p.w[14] * (txx * tyy * sm);
+  t[14] = fma_r(p.wc[14], c[14], p.w[14] * (txx * tyy * sm));
 
   // back through the inversion and the shifts central -> raw (z, y, x order
   // reversed: the forward applies z, then y, then x)
@@ -655,18 +650,18 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
     R v[15];   // input of the x shift = t shifted along z and y
 #pragma unroll
     for (int m = 0; m < 15; ++m) v[m] = t[m];
-    shift15<2>(v, uz, R(1));
-    shift15<1>(v, uy, R(1));
+    shift15_as_written<2>(v, uz);
+    shift15_as_written<1>(v, uy);
     shift15_adj<0>(v, ux, R(1), gt, gux);
-    shift15<1>(v, uy, R(-1));   // undo: v = input of the y shift
+    shift15_as_written<1>(v, -uy);   // undo: v = input of the y shift
     shift15_adj<1>(v, uy, R(1), gt, guy);
     shift15_adj<2>(t, uz, R(1), gt, guz);
   }
   // relaxation
   grho += gt[0];
-  gFx += R(0.5) * gt[1];
-  gFy += R(0.5) * gt[2];
-  gFz += R(0.5) * gt[3];
+  gFx = fma_r(R(0.5), gt[1], gFx);
+  gFy = fma_r(R(0.5), gt[2], gFy);
+  gFz = fma_r(R(0.5), gt[3], gFz);
   R gc[15];
   gc[0] = gc[1] = gc[2] = gc[3] = R(0);
 #pragma unroll
@@ -683,37 +678,38 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
   const R gtzz = gt[9];
   {
     const R G = gt[14];
-    const R A = txx * tyy * sm;
+    const R txy = txx * tyy;
     gc[14] = p.wc[14] * G;
-    add_product(gw, 14, A - c[14], G);
+    add_product(gw, 14, fma_r(txy, sm, -c[14]), G);
     const R gA = p.w[14] * G;
-    if (pm) grho -= sm * A * gA;
-    gtxx += gA * tyy * sm;
-    gtyy += gA * txx * sm;
+    if (pm) grho = fma_r(-sm * (txy * sm), gA, grho);
+    gtxx = fma_r(gA * tyy, sm, gtxx);
+    gtyy = fma_r(gA * txx, sm, gtyy);
   }
   {
-    const R gt9 = (gtxx + gtyy) * R(1.0 / 3.0) + gtzz * R(1.0 / 3.0);
-    const R gd2 = (gtxx + gtyy) * R(1.0 / 6.0) - gtzz * R(1.0 / 3.0);
+    const R gxy = gtxx + gtyy, gzz3 = gtzz * R(1.0 / 3.0);
+    const R gt9 = fma_r(gxy, R(1.0 / 3.0), gzz3);
+    const R gd2 = fma_r(gxy, R(1.0 / 6.0), -gzz3);
     const R gd1 = R(0.5) * (gtxx - gtyy);
-    sub_product(gw, 7, c[7] - c[8], gd1);
-    sub_product(gw, 8, c[7] + c[8] - R(2) * c[9], gd2);
-    add_product(gw, 9, rho - (c[7] + c[8] + c[9]), gt9);
-    grho += p.w[9] * gt9;
-    const R gD1 = p.wc[7] * gd1, gD2 = p.wc[8] * gd2, gT = p.wc[9] * gt9;
-    gc[7] = gD1 + gD2 + gT;
-    gc[8] = -gD1 + gD2 + gT;
-    gc[9] = R(-2) * gD2 + gT;
+    sub_product(gw, 7, D1, gd1);
+    sub_product(gw, 8, D2, gd2);
+    add_product(gw, 9, rho - T, gt9);
+    grho = fma_r(p.w[9], gt9, grho);
+    const R gD2 = p.wc[8] * gd2, gT = p.wc[9] * gt9;
+    gc[7] = fma_r(p.wc[9], gt9, fma_r(p.wc[7], gd1, gD2));
+    gc[8] = fma_r(p.wc[9], gt9, fma_r(-p.wc[7], gd1, gD2));
+    gc[9] = fma_r(R(-2), gD2, gT);
   }
   // back through the shifts raw -> central (forward order x, y, z)
   {
     R v[15];   // input of the z shift: c unshifted along z
 #pragma unroll
     for (int m = 0; m < 15; ++m) v[m] = c[m];
-    shift15<2>(v, uz, R(1));
+    shift15_as_written<2>(v, uz);
     shift15_adj<2>(v, uz, R(-1), gc, guz);
-    shift15<1>(v, uy, R(1));   // input of the y shift
+    shift15_as_written<1>(v, uy);   // input of the y shift
     shift15_adj<1>(v, uy, R(-1), gc, guy);
-    shift15<0>(v, ux, R(1));   // raw moments of h
+    shift15_as_written<0>(v, ux);   // raw moments of h
     shift15_adj<0>(v, ux, R(-1), gc, gux);
   }
   // raw moments (of f and of the source), density and velocity
@@ -722,13 +718,13 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
   source_raw15_adj(Fx, Fy, Fz, ux, uy, uz, gc, gFx, gFy, gFz, gux, guy, guz);
   const R inv = inv_rho;
   const R gjx = gux * inv, gjy = guy * inv, gjz = guz * inv;
-  grho -= (ux * gux + uy * guy + uz * guz) * inv;
-  gFx += R(0.5) * gjx;
-  gFy += R(0.5) * gjy;
-  gFz += R(0.5) * gjz;
+  grho = fma_r(-fma_r(uz, guz, fma_r(uy, guy, ux * gux)), inv, grho);
+  gFx = fma_r(R(0.5), gjx, gFx);
+  gFy = fma_r(R(0.5), gjy, gFy);
+  gFz = fma_r(R(0.5), gjz, gFz);
 #pragma unroll
   for (int a = 0; a < 15; ++a)
-    g[a] = gh[a] + grho + R(kE15[a].x) * gjx + R(kE15[a].y) * gjy + R(kE15[a].z) * gjz;
+    g[a] = fma_r(R(kE15[a].z), gjz, fma_r(R(kE15[a].y), gjy, fma_r(R(kE15[a].x), gjx, gh[a] + grho)));
 }
 
 // Adjoint of the force dependence of initial15 (u0 fixed): fbar = f^eq - S/2.

@@ -37,15 +37,24 @@ struct Rates {
   int per_mass;
 };
 
+// In a function that starts with this, the multiply-adds are those written
+// (fma_r) and no others.  Several sums of the collision and of its adjoint have two
+// products of which either could be fused; left to the compiler, the choice, and with it
+// the rounding, depends on the code around them, and the kernels that run the collision (two
+// buffers, in place, two steps in one pass) or the adjoint (with running sums or with
+// their factors kept) would not agree bit for bit.
+#define CMLBM_FMA_AS_WRITTEN _Pragma("clang fp contract(off)")
+
 // -- 3-point transforms along one axis --------------------------------------
 // Populations (p_-, p_0, p_+) -> central moments (k0, k1, k2) about u:
 // k_n = sum_e p_e (e - u)^n.
 template <typename R>
 CMLBM_HD void fwd_line(R& a, R& b, R& c, R u) {
+  CMLBM_FMA_AS_WRITTEN
   const R k0 = a + b + c;
   const R d = c - a;
-  const R k1 = d - u * k0;
-  const R k2 = (c + a) - u * (d + k1);
+  const R k1 = fma_r(-u, k0, d);
+  const R k2 = fma_r(-u, d + k1, c + a);
   a = k0;
   b = k1;
   c = k2;
@@ -73,43 +82,32 @@ CMLBM_HD void inv_line(R& a, R& b, R& c, R u) {
   b = m0 - r2;
 }
 
-// Adjoint of fwd_line: (a, b, c) are the forward inputs, (ga, gb, gc) hold
-// the adjoints of the outputs on entry and of the inputs on exit.
-template <typename R>
-CMLBM_HD void fwd_line_adj(R a, R b, R c, R u, R& ga, R& gb, R& gc, R& gu) {
-  const R k0 = a + b + c;
-  const R d = c - a;
-  const R k1 = d - u * k0;
-  const R g0 = ga, g1 = gb, g2 = gc;
-  gu -= (d + k1) * g2;
-  const R gt = -u * g2;                   // adjoint of (d + k1)
-  const R g1t = g1 + gt;
-  const R gd = gt + g1t;
-  gu -= k0 * g1t;
-  const R g0t = g0 - u * g1t;
-  ga = g2 - gd + g0t;
-  gb = g0t;
-  gc = g2 + gd + g0t;
+// inv_line with its multiply-adds as written.
+template <bool HALVE, typename R>
+CMLBM_HD void inv_line_as_written(R& a, R& b, R& c, R u) {
+  CMLBM_FMA_AS_WRITTEN
+  const R m0 = a, m1 = b, m2 = c;
+  const R r1 = fma_r(u, m0, m1);
+  const R r2 = fma_r(u, m1 + r1, m2);
+  a = HALVE ? R(0.5) * (r2 - r1) : r2 - r1;
+  b = m0 - r2;
+  c = HALVE ? R(0.5) * (r2 + r1) : r2 + r1;
 }
 
-// Adjoint of inv_line, same conventions.
+// Adjoint of inv_line: (m0, m1) are the forward inputs, (ga, gb, gc) hold the
+// adjoints of the outputs on entry and of the inputs on exit; adds to gu.
 template <typename R>
-CMLBM_HD void inv_line_adj(R m0, R m1, R m2, R u, R& ga, R& gb, R& gc, R& gu) {
-  const R r1 = m1 + u * m0;
+CMLBM_HD void inv_line_adj(R m0, R m1, R u, R& ga, R& gb, R& gc, R& gu) {
+  CMLBM_FMA_AS_WRITTEN
+  const R r1 = fma_r(u, m0, m1);
   const R pa = ga, pb = gb, pc = gc;
-  const R gr2 = R(0.5) * (pa + pc) - pb;
-  R gr1 = R(0.5) * (pc - pa);
-  R gm0 = pb;
-  const R gm2 = gr2;
-  gu += gr2 * (m1 + r1);
-  R gm1 = gr2 * u;
-  gr1 += gr2 * u;
-  gm1 += gr1;
-  gm0 += gr1 * u;
-  gu += gr1 * m0;
-  ga = gm0;
-  gb = gm1;
-  gc = gm2;
+  const R gr2 = fma_r(R(0.5), pa + pc, -pb);
+  const R gr1 = fma_r(gr2, u, R(0.5) * (pc - pa));
+  gu = fma_r(gr2, m1 + r1, gu);
+  gu = fma_r(gr1, m0, gu);
+  ga = fma_r(gr1, u, pb);
+  gb = fma_r(gr2, u, gr1);
+  gc = gr2;
 }
 
 // The forward transform of the step in two halves: raw moments first, one
@@ -128,16 +126,18 @@ CMLBM_HD void raw_line(R& a, R& b, R& c) {
 // Raw (r0, r1, r2) along an axis -> central (r0, r1 - u r0, r2 - 2 u r1 + u^2 r0).
 template <typename R>
 CMLBM_HD void shift_line(R a, R& b, R& c, R u) {
-  const R k1 = b - u * a;
-  c = c - u * (b + k1);
+  CMLBM_FMA_AS_WRITTEN
+  const R k1 = fma_r(-u, a, b);
+  c = fma_r(-u, b + k1, c);
   b = k1;
 }
 
 // Inverse of shift_line: central (k0, k1, k2) about u -> raw (r0, r1, r2).
 template <typename R>
 CMLBM_HD void unshift_line(R a, R& b, R& c, R u) {
-  const R r1 = b + u * a;
-  c = c + u * (r1 + b);
+  CMLBM_FMA_AS_WRITTEN
+  const R r1 = fma_r(u, a, b);
+  c = fma_r(u, r1 + b, c);
   b = r1;
 }
 
@@ -146,10 +146,11 @@ CMLBM_HD void unshift_line(R a, R& b, R& c, R u) {
 // k1 = r1 - u r0 and k2 = r2 - u (r1 + k1), dk2/du = -2 k1 and dk1/du = -k0.
 template <typename R>
 CMLBM_HD void shift_line_adj(R k0, R k1, R u, R& g0, R& g1, R g2, R& gu) {
-  gu -= k0 * g1 + R(2) * k1 * g2;
-  const R t = g1 - u * g2;
-  g0 = g0 - u * t;
-  g1 = t - u * g2;
+  CMLBM_FMA_AS_WRITTEN
+  gu -= fma_r(k0, g1, R(2) * k1 * g2);
+  const R t = fma_r(-u, g2, g1);
+  g0 = fma_r(-u, t, g0);
+  g1 = fma_r(-u, g2, t);
 }
 
 // Adjoint of raw_line (a linear map): (ga, gb, gc) hold the adjoints of
@@ -213,21 +214,13 @@ CMLBM_HD void unshift_pass(R (&m)[27], R u) {
   }
 }
 
-// m: the output of shift_pass<AXIS> (central moments along AXIS).  FUSE: a line
-// whose first product of the sum for gu is the fused one (-1: the compiler's choice
-// everywhere).
-template <int AXIS, int FUSE = -1, typename R>
+// m: the output of shift_pass<AXIS> (central moments along AXIS).
+template <int AXIS, typename R>
 CMLBM_HD void shift_pass_adj(const R (&m)[27], R u, R (&g)[27], R& gu) {
   constexpr int S = line_stride<AXIS>();
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
     const int o = line_base<AXIS>(l);
-    if (l == FUSE) {
-      gu -= fma_r(m[o], g[o + S], R(2) * m[o + S] * g[o + 2 * S]);
-      R none = R(0);
-      shift_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], none);
-      continue;
-    }
     shift_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], gu);
   }
 }
@@ -252,13 +245,13 @@ CMLBM_HD void inv_pass(R (&m)[27], R u) {
   }
 }
 
-template <int AXIS, typename R>
-CMLBM_HD void fwd_pass_adj(const R (&m)[27], R u, R (&g)[27], R& gu) {
+template <int AXIS, bool HALVE = true, typename R>
+CMLBM_HD void inv_pass_as_written(R (&m)[27], R u) {
   constexpr int S = line_stride<AXIS>();
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
     const int o = line_base<AXIS>(l);
-    fwd_line_adj(m[o], m[o + S], m[o + 2 * S], u, g[o], g[o + S], g[o + 2 * S], gu);
+    inv_line_as_written<HALVE>(m[o], m[o + S], m[o + 2 * S], u);
   }
 }
 
@@ -268,14 +261,34 @@ CMLBM_HD void inv_pass_adj(const R (&m)[27], R u, R (&g)[27], R& gu) {
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
     const int o = line_base<AXIS>(l);
-    inv_line_adj(m[o], m[o + S], m[o + 2 * S], u, g[o], g[o + S], g[o + 2 * S], gu);
+    inv_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], gu);
   }
 }
+
+// The diagonal second moments: their combinations D1 = xx - yy, D2 = xx + yy - 2 zz and
+// T = xx + yy + zz (g7, g8 relaxed toward 0, g9 toward rho) and the relaxed ones.
+template <typename R>
+struct Diagonal27 {
+  R D1, D2, T, kxx, kyy, kzz;
+  CMLBM_HD Diagonal27(R xx, R yy, R zz, R rho, const Rates<R>& p) {
+    CMLBM_FMA_AS_WRITTEN
+    const R xy2 = xx + yy;
+    D1 = xx - yy;
+    D2 = fma_r(R(-2), zz, xy2);
+    T = xy2 + zz;
+    const R t = fma_r(p.w[9], rho, p.wc[9] * T);
+    const R d1 = p.wc[7] * D1, td = fma_r(R(2), t, p.wc[8] * D2);
+    kxx = fma_r(R(3), d1, td) * R(1.0 / 6.0);
+    kyy = fma_r(R(-3), d1, td) * R(1.0 / 6.0);
+    kzz = fma_r(-p.wc[8], D2, t) * R(1.0 / 3.0);
+  }
+};
 
 // Relax the central moments in m (cube layout) in place.  PM: attractor form,
 // 0 literal, 1 per unit mass, -1 as p.per_mass says (run time).
 template <int PM = -1, typename R>
 CMLBM_HD void relax27(R (&m)[27], R rho, R inv_rho, R Fx, R Fy, R Fz, const Rates<R>& p) {
+  CMLBM_FMA_AS_WRITTEN
   const bool pm = PM < 0 ? p.per_mass != 0 : PM != 0;
   // conserved: density and first central moments F/2
   m[K3(0, 0, 0)] = rho;
@@ -286,49 +299,35 @@ CMLBM_HD void relax27(R (&m)[27], R rho, R inv_rho, R Fx, R Fy, R Fz, const Rate
   m[K3(1, 1, 0)] *= p.wc[4];
   m[K3(1, 0, 1)] *= p.wc[5];
   m[K3(0, 1, 1)] *= p.wc[6];
-  // second order, diagonal: xx-yy (g7), xx+yy-2zz (g8) toward 0, xx+yy+zz (g9) toward rho
-  const R xx = m[K3(2, 0, 0)], yy = m[K3(0, 2, 0)], zz = m[K3(0, 0, 2)];
-  const R d1 = p.wc[7] * (xx - yy);
-  const R d2 = p.wc[8] * (xx + yy - R(2) * zz);
-  const R t = p.wc[9] * (xx + yy + zz) + p.w[9] * rho;
-  const R kxx = (R(2) * t + d2 + R(3) * d1) * R(1.0 / 6.0);
-  const R kyy = (R(2) * t + d2 - R(3) * d1) * R(1.0 / 6.0);
-  const R kzz = (t - d2) * R(1.0 / 3.0);
-  m[K3(2, 0, 0)] = kxx;
-  m[K3(0, 2, 0)] = kyy;
-  m[K3(0, 0, 2)] = kzz;
+  // second order, diagonal
+  const Diagonal27<R> k(m[K3(2, 0, 0)], m[K3(0, 2, 0)], m[K3(0, 0, 2)], rho, p);
+  m[K3(2, 0, 0)] = k.kxx;
+  m[K3(0, 2, 0)] = k.kyy;
+  m[K3(0, 0, 2)] = k.kzz;
   // third order: xyy+xzz (g10) with xyy-xzz (g13), and the y, z analogues
-  {
-    const R s = p.wc[10] * (m[K3(1, 2, 0)] + m[K3(1, 0, 2)]);
-    const R d = p.wc[13] * (m[K3(1, 2, 0)] - m[K3(1, 0, 2)]);
-    m[K3(1, 2, 0)] = R(0.5) * (s + d);
-    m[K3(1, 0, 2)] = R(0.5) * (s - d);
-  }
-  {
-    const R s = p.wc[11] * (m[K3(2, 1, 0)] + m[K3(0, 1, 2)]);
-    const R d = p.wc[14] * (m[K3(2, 1, 0)] - m[K3(0, 1, 2)]);
-    m[K3(2, 1, 0)] = R(0.5) * (s + d);
-    m[K3(0, 1, 2)] = R(0.5) * (s - d);
-  }
-  {
-    const R s = p.wc[12] * (m[K3(2, 0, 1)] + m[K3(0, 2, 1)]);
-    const R d = p.wc[15] * (m[K3(2, 0, 1)] - m[K3(0, 2, 1)]);
-    m[K3(2, 0, 1)] = R(0.5) * (s + d);
-    m[K3(0, 2, 1)] = R(0.5) * (s - d);
-  }
+  auto pair = [&](int i, int j, int bs, int bd) {
+    CMLBM_FMA_AS_WRITTEN
+    const R s = m[i] + m[j], d = p.wc[bd] * (m[i] - m[j]);
+    m[i] = R(0.5) * fma_r(p.wc[bs], s, d);
+    m[j] = R(0.5) * fma_r(p.wc[bs], s, -d);
+  };
+  pair(K3(1, 2, 0), K3(1, 0, 2), 10, 13);
+  pair(K3(2, 1, 0), K3(0, 1, 2), 11, 14);
+  pair(K3(2, 0, 1), K3(0, 2, 1), 12, 15);
   m[K3(1, 1, 1)] *= p.wc[16];
   // fourth order, diagonal pairs (g17, g18, g19) toward the factorized attractors
   const R sm = pm ? inv_rho : R(1);
+  const R kys = k.kyy * sm, kzs = k.kzz * sm;
   {
-    const R axy = kxx * kyy * sm, axz = kxx * kzz * sm, ayz = kyy * kzz * sm;
+    const R axz = k.kxx * kzs, ayz = k.kyy * kzs, axy_xz = fma_r(k.kxx, kys, axz);
     const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
-    const R q1 = p.wc[17] * (A + B + C) + p.w[17] * (axy + axz + ayz);
-    const R q2 = p.wc[18] * (A + B - R(2) * C) + p.w[18] * (axy + axz - R(2) * ayz);
-    const R q3 = p.wc[19] * (A - B) + p.w[19] * (axy - axz);
-    const R ab = (R(2) * q1 + q2) * R(1.0 / 3.0);
+    const R q1 = fma_r(p.wc[17], A + B + C, p.w[17] * (axy_xz + ayz));
+    const R q2 = fma_r(p.wc[18], fma_r(R(-2), C, A + B), p.w[18] * fma_r(R(-2), ayz, axy_xz));
+    const R q3 = fma_r(p.wc[19], A - B, p.w[19] * fma_r(k.kxx, kys, -axz));
+    const R ab = fma_r(R(2), q1, q2);
     m[K3(0, 2, 2)] = (q1 - q2) * R(1.0 / 3.0);
-    m[K3(2, 2, 0)] = R(0.5) * (ab + q3);
-    m[K3(2, 0, 2)] = R(0.5) * (ab - q3);
+    m[K3(2, 2, 0)] = R(0.5) * fma_r(ab, R(1.0 / 3.0), q3);
+    m[K3(2, 0, 2)] = R(0.5) * fma_r(ab, R(1.0 / 3.0), -q3);
   }
   m[K3(2, 1, 1)] *= p.wc[20];
   m[K3(1, 2, 1)] *= p.wc[21];
@@ -338,60 +337,7 @@ CMLBM_HD void relax27(R (&m)[27], R rho, R inv_rho, R Fx, R Fy, R Fz, const Rate
   m[K3(2, 1, 2)] *= p.wc[24];
   m[K3(2, 2, 1)] *= p.wc[25];
   // sixth order toward kxx kyy kzz (g26)
-  m[K3(2, 2, 2)] = p.wc[26] * m[K3(2, 2, 2)] + p.w[26] * (kxx * kyy * kzz * (sm * sm));
-}
-
-// First pass along z fused with the density and velocity sums: raw z-moments
-// (s0, s1, s2) = (a+b+c, c-a, c+a) of each line give rho and j, then the shift
-// to central moments about u_z is the same arithmetic as fwd_line.
-template <typename R>
-CMLBM_HD void first_pass27(R (&m)[27], R Fx, R Fy, R Fz, R& rho, R& ux, R& uy, R& uz, R& inv_rho) {
-  R s0[9], s1[9];
-#pragma unroll
-  for (int l = 0; l < 9; ++l) {
-    const int o = line_base<2>(l);
-    s0[l] = m[o] + m[o + 1] + m[o + 2];
-    s1[l] = m[o + 2] - m[o];
-  }
-  // lines l = ix*3 + iy
-  rho = ((s0[0] + s0[1] + s0[2]) + (s0[3] + s0[4] + s0[5])) + (s0[6] + s0[7] + s0[8]);
-  const R jx = (s0[6] + s0[7] + s0[8]) - (s0[0] + s0[1] + s0[2]);
-  const R jy = (s0[2] + s0[5] + s0[8]) - (s0[0] + s0[3] + s0[6]);
-  const R jz = ((s1[0] + s1[1] + s1[2]) + (s1[3] + s1[4] + s1[5])) + (s1[6] + s1[7] + s1[8]);
-  const R inv = recip(rho);
-  inv_rho = inv;
-  ux = (jx + R(0.5) * Fx) * inv;
-  uy = (jy + R(0.5) * Fy) * inv;
-  uz = (jz + R(0.5) * Fz) * inv;
-#pragma unroll
-  for (int l = 0; l < 9; ++l) {
-    const int o = line_base<2>(l);
-    const R k1 = s1[l] - uz * s0[l];
-    const R k2 = (m[o + 2] + m[o]) - uz * (s1[l] + k1);
-    m[o] = s0[l];
-    m[o + 1] = k1;
-    m[o + 2] = k2;
-  }
-}
-
-// In a function that starts with this, the multiply-adds are those written
-// (fma_r) and no others.  Several sums of the relaxation have two products of
-// which either could be fused; left to the compiler, the choice, and with it the
-// rounding, depends on the code around the collision, and the kernels that run it
-// (two buffers, in place, two steps in one pass) would not agree bit for bit.
-#define CMLBM_FMA_AS_WRITTEN _Pragma("clang fp contract(off)")
-
-template <int AXIS, typename R>
-CMLBM_HD void shift_pass_as_written(R (&m)[27], R u) {
-  CMLBM_FMA_AS_WRITTEN
-  constexpr int S = line_stride<AXIS>();
-#pragma unroll
-  for (int l = 0; l < 9; ++l) {
-    const int o = line_base<AXIS>(l);
-    const R k1 = fma_r(-u, m[o], m[o + S]);
-    m[o + 2 * S] = fma_r(-u, m[o + S] + k1, m[o + 2 * S]);
-    m[o + S] = k1;
-  }
+  m[K3(2, 2, 2)] = fma_r(p.wc[26], m[K3(2, 2, 2)], p.w[26] * (k.kxx * kys * kzs));
 }
 
 // The relaxation of relax27 and the inverse pass along x (inv_pass<0, false>) in
@@ -478,25 +424,24 @@ CMLBM_HD void relax_unshift_x27(R (&m)[27], R rho, R inv_rho, R ux, R Fx, R Fy, 
 // Full collision: cube-ordered pre-collision populations in, post-collision out.
 template <typename R>
 CMLBM_HD void collide27(R (&m)[27], R Fx, R Fy, R Fz, const Rates<R>& p) {
+  CMLBM_FMA_AS_WRITTEN
   raw_pass<2>(m);
   raw_pass<1>(m);
   raw_pass<0>(m);
   const R rho = m[K3(0, 0, 0)];
   const R inv_rho = recip(rho);
-  // (explicit fused multiply-adds: the rounding of u must not depend on what
-  // else the kernel computes from 0.5 F)
   const R ux = fma_r(R(0.5), Fx, m[K3(1, 0, 0)]) * inv_rho;
   const R uy = fma_r(R(0.5), Fy, m[K3(0, 1, 0)]) * inv_rho;
   const R uz = fma_r(R(0.5), Fz, m[K3(0, 0, 1)]) * inv_rho;
-  shift_pass_as_written<0>(m, ux);
-  shift_pass_as_written<1>(m, uy);
-  shift_pass_as_written<2>(m, uz);
+  shift_pass<0>(m, ux);
+  shift_pass<1>(m, uy);
+  shift_pass<2>(m, uz);
   // the three inverse passes without their halvings, then population e scaled
   // by 2^-(number of nonzero components of e) (one multiply each, which a
   // 16-bit store fuses with its subtraction of the rest weight)
   relax_unshift_x27(m, rho, inv_rho, ux, Fx, Fy, Fz, p);
-  inv_pass<1, false>(m, uy);
-  inv_pass<2, false>(m, uz);
+  inv_pass_as_written<1, false>(m, uy);
+  inv_pass_as_written<2, false>(m, uz);
 #pragma unroll
   for (int i = 0; i < 27; ++i) {
     const int k = (i / 9 != 1) + ((i / 3) % 3 != 1) + (i % 3 != 1);
@@ -509,22 +454,11 @@ CMLBM_HD void collide27(R (&m)[27], R Fx, R Fy, R Fz, const Rates<R>& p) {
 // overload these).
 template <typename W, typename R>
 CMLBM_HD void add_product(W& gw, int b, R x, R g) {
-  gw[b] += x * g;
+  gw[b] = fma_r(x, g, R(gw[b]));
 }
 template <typename W, typename R>
 CMLBM_HD void sub_product(W& gw, int b, R x, R g) {
-  gw[b] -= x * g;
-}
-
-// The line of the y shift's adjoint whose products collide27_adj has to fuse in a given
-// way (see shift_pass_adj), by accumulator.
-template <typename W>
-struct FusedLine {
-  static constexpr int value = -1;
-};
-template <typename W>
-CMLBM_HD constexpr int fused_line() {
-  return FusedLine<W>::value;
+  add_product(gw, b, -x, g);
 }
 
 // Adjoint of relax27.  m: pre-relaxation central moments (unchanged).  g: on
@@ -533,110 +467,103 @@ CMLBM_HD constexpr int fused_line() {
 template <int PM = -1, typename R, typename W>
 CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27], R& grho,
                                             R& gFx, R& gFy, R& gFz, W& gw) {
+  CMLBM_FMA_AS_WRITTEN
   const bool pm = PM < 0 ? p.per_mass != 0 : PM != 0;
   // recompute the second-order post values and attractor inputs
-  const R xx = m[K3(2, 0, 0)], yy = m[K3(0, 2, 0)], zz = m[K3(0, 0, 2)];
-  const R D1 = xx - yy, D2 = xx + yy - R(2) * zz, T = xx + yy + zz;
-  const R d1 = p.wc[7] * D1, d2 = p.wc[8] * D2, t = p.wc[9] * T + p.w[9] * rho;
-  const R kxx = (R(2) * t + d2 + R(3) * d1) * R(1.0 / 6.0);
-  const R kyy = (R(2) * t + d2 - R(3) * d1) * R(1.0 / 6.0);
-  const R kzz = (t - d2) * R(1.0 / 3.0);
-  R gkxx = R(0), gkyy = R(0), gkzz = R(0);
+  const Diagonal27<R> k(m[K3(2, 0, 0)], m[K3(0, 2, 0)], m[K3(0, 0, 2)], rho, p);
+  const R kxx = k.kxx, kyy = k.kyy, kzz = k.kzz;
   // per-mass attractors: A = P sm^(k-1), dA/drho = -(k-1) A sm
   const R sm = pm ? R(1) / rho : R(1);
+  R gkxx, gkyy, gkzz;
 
   // sixth order
   {
     const R G = g[K3(2, 2, 2)];
-    const R s2 = sm * sm;
-    const R P = kxx * kyy * kzz * s2;
-    add_product(gw, 26, P - m[K3(2, 2, 2)], G);
+    const R s2 = sm * sm, kxy = kxx * kyy, kzs2 = kzz * s2;
+    add_product(gw, 26, fma_r(kxy, kzs2, -m[K3(2, 2, 2)]), G);
     const R gP = p.w[26] * G;
-    if (pm) grho -= R(2) * sm * P * gP;
+    if (pm) grho = fma_r(R(-2) * sm * (kxy * kzs2), gP, grho);
     const R gPs = gP * s2;
-    gkxx += gPs * kyy * kzz;
-    gkyy += gPs * kxx * kzz;
-    gkzz += gPs * kxx * kyy;
+    gkxx = gPs * kyy * kzz;
+    gkyy = gPs * kxx * kzz;
+    gkzz = gPs * kxx * kyy;
     g[K3(2, 2, 2)] = p.wc[26] * G;
   }
   // fifth order and fourth-order off-diagonal: m~ = (1 - w) m
-#define CMLBM_SCALE_ADJ(I, B)         \
-  {                                   \
-    const R G = g[I];                 \
-    sub_product(gw, B, m[I], G);     \
-    g[I] = p.wc[B] * G;               \
-  }
-  CMLBM_SCALE_ADJ(K3(1, 2, 2), 23)
-  CMLBM_SCALE_ADJ(K3(2, 1, 2), 24)
-  CMLBM_SCALE_ADJ(K3(2, 2, 1), 25)
-  CMLBM_SCALE_ADJ(K3(2, 1, 1), 20)
-  CMLBM_SCALE_ADJ(K3(1, 2, 1), 21)
-  CMLBM_SCALE_ADJ(K3(1, 1, 2), 22)
+  auto scale = [&](int i, int b) {
+    const R G = g[i];
+    sub_product(gw, b, m[i], G);
+    g[i] = p.wc[b] * G;
+  };
+  scale(K3(1, 2, 2), 23);
+  scale(K3(2, 1, 2), 24);
+  scale(K3(2, 2, 1), 25);
+  scale(K3(2, 1, 1), 20);
+  scale(K3(1, 2, 1), 21);
+  scale(K3(1, 1, 2), 22);
   // fourth order diagonal
   {
-    const R axy = kxx * kyy * sm, axz = kxx * kzz * sm, ayz = kyy * kzz * sm;
+    const R kys = kyy * sm, kzs = kzz * sm;
+    const R axz = kxx * kzs, ayz = kyy * kzs, axy_xz = fma_r(kxx, kys, axz);
     const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
-    const R Q1 = A + B + C, Q2 = A + B - R(2) * C, Q3 = A - B;
-    const R a1 = axy + axz + ayz, a2 = axy + axz - R(2) * ayz, a3 = axy - axz;
     const R gA = g[K3(2, 2, 0)], gB = g[K3(2, 0, 2)], gC = g[K3(0, 2, 2)];
-    const R gab = R(0.5) * (gA + gB);
+    const R gAB = gA + gB;                                       // twice the adjoint of A + B
     const R gq3 = R(0.5) * (gA - gB);
-    const R gq1 = (gC + R(2) * gab) * R(1.0 / 3.0);
-    const R gq2 = (gab - gC) * R(1.0 / 3.0);
-    add_product(gw, 17, a1 - Q1, gq1);
-    add_product(gw, 18, a2 - Q2, gq2);
-    add_product(gw, 19, a3 - Q3, gq3);
-    const R ga1 = p.w[17] * gq1, ga2 = p.w[18] * gq2, ga3 = p.w[19] * gq3;
-    const R gQ1 = p.wc[17] * gq1, gQ2 = p.wc[18] * gq2, gQ3 = p.wc[19] * gq3;
-    const R gaxy = ga1 + ga2 + ga3, gaxz = ga1 + ga2 - ga3, gayz = ga1 - R(2) * ga2;
-    if (pm) grho -= sm * (axy * gaxy + axz * gaxz + ayz * gayz);
-    gkxx += sm * (gaxy * kyy + gaxz * kzz);
-    gkyy += sm * (gaxy * kxx + gayz * kzz);
-    gkzz += sm * (gaxz * kxx + gayz * kyy);
-    g[K3(2, 2, 0)] = gQ1 + gQ2 + gQ3;
-    g[K3(2, 0, 2)] = gQ1 + gQ2 - gQ3;
-    g[K3(0, 2, 2)] = gQ1 - R(2) * gQ2;
+    const R gq1 = (gC + gAB) * R(1.0 / 3.0);
+    const R gq2 = fma_r(R(0.5), gAB, -gC) * R(1.0 / 3.0);
+    add_product(gw, 17, fma_r(kyy, kzs, axy_xz) - (A + B + C), gq1);
+    add_product(gw, 18, fma_r(R(-2), ayz, axy_xz) - fma_r(R(-2), C, A + B), gq2);
+    add_product(gw, 19, fma_r(kxx, kys, -axz) - (A - B), gq3);
+    const R ga1 = p.w[17] * gq1, ga2 = p.w[18] * gq2, ga12 = fma_r(p.w[18], gq2, ga1);
+    const R gaxy = fma_r(p.w[19], gq3, ga12), gaxz = fma_r(-p.w[19], gq3, ga12), gayz = fma_r(R(-2), ga2, ga1);
+    if (pm) grho = fma_r(-sm, fma_r(ayz, gayz, fma_r(axz, gaxz, kxx * kys * gaxy)), grho);
+    gkxx = fma_r(sm, fma_r(gaxy, kyy, gaxz * kzz), gkxx);
+    gkyy = fma_r(sm, fma_r(gayz, kzz, gaxy * kxx), gkyy);
+    gkzz = fma_r(sm, fma_r(gayz, kyy, gaxz * kxx), gkzz);
+    const R gQ1 = p.wc[17] * gq1, gQ2 = p.wc[18] * gq2, gQ12 = fma_r(p.wc[18], gq2, gQ1);
+    g[K3(2, 2, 0)] = fma_r(p.wc[19], gq3, gQ12);
+    g[K3(2, 0, 2)] = fma_r(-p.wc[19], gq3, gQ12);
+    g[K3(0, 2, 2)] = fma_r(R(-2), gQ2, gQ1);
   }
   // third order
-  CMLBM_SCALE_ADJ(K3(1, 1, 1), 16)
-#define CMLBM_PAIR_ADJ(IA, IB, BS, BD)                  \
-  {                                                     \
-    const R gs = R(0.5) * (g[IA] + g[IB]);              \
-    const R gd = R(0.5) * (g[IA] - g[IB]);              \
-    sub_product(gw, BS, m[IA] + m[IB], gs);          \
-    sub_product(gw, BD, m[IA] - m[IB], gd);          \
-    const R a = p.wc[BS] * gs, b = p.wc[BD] * gd;       \
-    g[IA] = a + b;                                      \
-    g[IB] = a - b;                                      \
-  }
-  CMLBM_PAIR_ADJ(K3(1, 2, 0), K3(1, 0, 2), 10, 13)
-  CMLBM_PAIR_ADJ(K3(2, 1, 0), K3(0, 1, 2), 11, 14)
-  CMLBM_PAIR_ADJ(K3(2, 0, 1), K3(0, 2, 1), 12, 15)
-#undef CMLBM_PAIR_ADJ
+  scale(K3(1, 1, 1), 16);
+  auto pair = [&](int i, int j, int bs, int bd) {
+    CMLBM_FMA_AS_WRITTEN
+    const R gs = R(0.5) * (g[i] + g[j]);
+    const R gd = R(0.5) * (g[i] - g[j]);
+    sub_product(gw, bs, m[i] + m[j], gs);
+    sub_product(gw, bd, m[i] - m[j], gd);
+    const R b = p.wc[bd] * gd;
+    g[i] = fma_r(p.wc[bs], gs, b);
+    g[j] = fma_r(p.wc[bs], gs, -b);
+  };
+  pair(K3(1, 2, 0), K3(1, 0, 2), 10, 13);
+  pair(K3(2, 1, 0), K3(0, 1, 2), 11, 14);
+  pair(K3(2, 0, 1), K3(0, 2, 1), 12, 15);
   // second order diagonal; total adjoint of kxx, kyy, kzz
   {
     const R Gx = g[K3(2, 0, 0)] + gkxx, Gy = g[K3(0, 2, 0)] + gkyy, Gz = g[K3(0, 0, 2)] + gkzz;
-    const R gt = (Gx + Gy) * R(1.0 / 3.0) + Gz * R(1.0 / 3.0);
-    const R gd2 = (Gx + Gy) * R(1.0 / 6.0) - Gz * R(1.0 / 3.0);
+    const R Gxy = Gx + Gy, Gz3 = Gz * R(1.0 / 3.0);
+    const R gt = fma_r(Gxy, R(1.0 / 3.0), Gz3);
+    const R gd2 = fma_r(Gxy, R(1.0 / 6.0), -Gz3);
     const R gd1 = R(0.5) * (Gx - Gy);
-    sub_product(gw, 7, D1, gd1);
-    sub_product(gw, 8, D2, gd2);
-    add_product(gw, 9, rho - T, gt);
-    grho += p.w[9] * gt;
-    const R gD1 = p.wc[7] * gd1, gD2 = p.wc[8] * gd2, gT = p.wc[9] * gt;
-    g[K3(2, 0, 0)] = gD1 + gD2 + gT;
-    g[K3(0, 2, 0)] = -gD1 + gD2 + gT;
-    g[K3(0, 0, 2)] = R(-2) * gD2 + gT;
+    sub_product(gw, 7, k.D1, gd1);
+    sub_product(gw, 8, k.D2, gd2);
+    add_product(gw, 9, rho - k.T, gt);
+    grho = fma_r(p.w[9], gt, grho);
+    const R gD2 = p.wc[8] * gd2, gT = p.wc[9] * gt;
+    g[K3(2, 0, 0)] = fma_r(p.wc[9], gt, fma_r(p.wc[7], gd1, gD2));
+    g[K3(0, 2, 0)] = fma_r(p.wc[9], gt, fma_r(-p.wc[7], gd1, gD2));
+    g[K3(0, 0, 2)] = fma_r(R(-2), gD2, gT);
   }
-  CMLBM_SCALE_ADJ(K3(1, 1, 0), 4)
-  CMLBM_SCALE_ADJ(K3(1, 0, 1), 5)
-  CMLBM_SCALE_ADJ(K3(0, 1, 1), 6)
-#undef CMLBM_SCALE_ADJ
+  scale(K3(1, 1, 0), 4);
+  scale(K3(1, 0, 1), 5);
+  scale(K3(0, 1, 1), 6);
   // conserved rows were overwritten by rho and F/2
   grho += g[K3(0, 0, 0)];
-  gFx += R(0.5) * g[K3(1, 0, 0)];
-  gFy += R(0.5) * g[K3(0, 1, 0)];
-  gFz += R(0.5) * g[K3(0, 0, 1)];
+  gFx = fma_r(R(0.5), g[K3(1, 0, 0)], gFx);
+  gFy = fma_r(R(0.5), g[K3(0, 1, 0)], gFy);
+  gFz = fma_r(R(0.5), g[K3(0, 0, 1)], gFz);
   g[K3(0, 0, 0)] = g[K3(1, 0, 0)] = g[K3(0, 1, 0)] = g[K3(0, 0, 1)] = R(0);
 }
 
@@ -653,6 +580,7 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
 template <int PM = -1, typename R, typename W>
 CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (&g)[27], R (&s)[27],
                                               R& gFx, R& gFy, R& gFz, W& gw) {
+  CMLBM_FMA_AS_WRITTEN
   R(&cm)[27] = f;
   raw_pass<2>(cm);
   raw_pass<1>(cm);
@@ -671,8 +599,8 @@ CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (
 #pragma unroll
   for (int k = 0; k < 27; ++k) s[k] = cm[k];
   relax27<PM>(s, rho, inv_rho, Fx, Fy, Fz, p);
-  inv_pass<0>(s, ux);
-  inv_pass<1>(s, uy);                        // s = input of the z inverse pass
+  inv_pass_as_written<0>(s, ux);
+  inv_pass_as_written<1>(s, uy);             // s = input of the z inverse pass
   inv_pass_adj<2>(s, uz, g, guz);
   fwd_pass<1>(s, uy);                        // undo the y pass: s = input of the y inverse pass
   inv_pass_adj<1>(s, uy, g, guy);
@@ -685,19 +613,18 @@ CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (
   // differentiated
   shift_pass_adj<2>(cm, uz, g, guz);
   unshift_pass<2>(cm, uz);
-  shift_pass_adj<1, fused_line<W>()>(cm, uy, g, guy);
+  shift_pass_adj<1>(cm, uy, g, guy);
   unshift_pass<1>(cm, uy);
   shift_pass_adj<0>(cm, ux, g, gux);
 
   // u = (j + F/2) / rho with j and rho the raw moments 100, 010, 001 and 000
-  const R gjx = gux * inv_rho, gjy = guy * inv_rho, gjz = guz * inv_rho;
-  g[K3(0, 0, 0)] += grho - (ux * gux + uy * guy + uz * guz) * inv_rho;
-  g[K3(1, 0, 0)] += gjx;
-  g[K3(0, 1, 0)] += gjy;
-  g[K3(0, 0, 1)] += gjz;
-  gFx += R(0.5) * gjx;
-  gFy += R(0.5) * gjy;
-  gFz += R(0.5) * gjz;
+  g[K3(0, 0, 0)] += fma_r(-fma_r(uz, guz, fma_r(uy, guy, ux * gux)), inv_rho, grho);
+  g[K3(1, 0, 0)] = fma_r(gux, inv_rho, g[K3(1, 0, 0)]);
+  g[K3(0, 1, 0)] = fma_r(guy, inv_rho, g[K3(0, 1, 0)]);
+  g[K3(0, 0, 1)] = fma_r(guz, inv_rho, g[K3(0, 0, 1)]);
+  gFx = fma_r(R(0.5), gux * inv_rho, gFx);
+  gFy = fma_r(R(0.5), guy * inv_rho, gFy);
+  gFz = fma_r(R(0.5), guz * inv_rho, gFz);
   raw_pass_adj<0>(g);
   raw_pass_adj<1>(g);
   raw_pass_adj<2>(g);

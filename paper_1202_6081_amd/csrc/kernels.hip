@@ -768,8 +768,11 @@ struct LdsColumn {
   __device__ __forceinline__ R& operator[](int b) const { return p[(b - 4) * kAdjBlock]; }
 };
 
-// Waves per SIMD the adjoint is compiled for: three 27-vectors and the line
-// transforms fit 168 VGPRs in FP32 (3 waves); FP64 needs twice the registers.
+// Waves per SIMD the adjoint is compiled for, at least and at most: three 27-vectors
+// and the line transforms fit 168 VGPRs in FP32 (3 waves); FP64 needs twice the
+// registers.  D3Q27 without walls would fit 128 in FP32, but a fourth wave is no gain: its
+// gathers evict what the others share (320 x 320 x 256 1740 against 1726 us, 128^3 165
+// against 157, 96^3 75 against 70; 200 x 90 x 80 131 against 134).
 #ifndef CMLBM_ADJ_WAVES_F32
 #define CMLBM_ADJ_WAVES_F32 3
 #endif
@@ -779,6 +782,10 @@ struct LdsColumn {
 template <class ST, bool MASK>
 constexpr int adjoint_waves() {
   return sizeof(typename ST::R) == 8 ? CMLBM_ADJ_WAVES_F64 : (MASK ? 3 : CMLBM_ADJ_WAVES_F32);
+}
+template <int Q, class ST, bool MASK>
+constexpr int adjoint_most_waves() {
+  return Q == 27 && sizeof(typename ST::R) == 4 ? adjoint_waves<ST, MASK>() : 8;
 }
 
 // The node count as a value the compiler must take as new at each use (an
@@ -821,19 +828,12 @@ __device__ __forceinline__ void sub_product(Products<NB, R>& w, int b, R x, R g)
   add_product(w, b, -x, g);
 }
 
-// Without the running sums the compiler would fuse the other product of this line
-// than in the other form.  (So that lambda has the same bits in both, found by comparing the
-// two kernels' instructions product by product.)
-template <int NB>
-struct FusedLine<Products<NB, float>> {
-  static constexpr int value = 5;
-};
-
 // PM: attractor form compiled in (0 literal, 1 per unit mass); the host picks
 // the instance that matches the rates' per_mass flag.
 template <int Q, class ST, bool MASK, int PM, bool SPLIT>
 __global__ __launch_bounds__(SPLIT ? kAdjSplitBlock : kAdjBlock)
-    __attribute__((amdgpu_waves_per_eu(SPLIT ? 1 : adjoint_waves<ST, MASK>()))) void k_adjoint(
+    __attribute__((amdgpu_waves_per_eu(SPLIT ? 1 : adjoint_waves<ST, MASK>(),
+                                       SPLIT ? 8 : adjoint_most_waves<Q, ST, MASK>()))) void k_adjoint(
         AdjArgs<typename ST::R> args, double* partials, uint32_t segment) {
   using R = typename ST::R;
   using T = typename ST::T;
@@ -946,12 +946,6 @@ __global__ __launch_bounds__(SPLIT ? kAdjSplitBlock : kAdjBlock)
       Fx = R(args.force.uni[0]);
       Fy = R(args.force.uni[1]);
       Fz = R(args.force.uni[2]);
-    }
-    if constexpr (SPLIT) {
-      // (taken as new here: the products with F are then fused as in the other form)
-      asm volatile("" : "+v"(Fx));
-      asm volatile("" : "+v"(Fy));
-      asm volatile("" : "+v"(Fz));
     }
     R gFx = R(0), gFy = R(0), gFz = R(0);
     if constexpr (Q == 27) {
