@@ -558,14 +558,26 @@ __global__ __launch_bounds__(256) void k_macro(AuxArgs<typename ST::R> args) {
   }
 }
 
-// Block sum of NV doubles held one set per thread; thread 0 gets the result.
+// Sum over the wavefront's lanes, in lane 0.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// The same of k v, with half of the products inside a multiply-add.
+__device__ __forceinline__ double wave_sum(double v, double k) {
+  CMLBM_FMA_AS_WRITTEN
+  const double kv = k * v;
+  double s = fma_r(k, v, __shfl_xor(kv, 32, 64));
+#pragma unroll
+  for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
+// The block's sum of NV doubles from their wavefronts' (in lane 0), in thread 0.
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double* sh /* [NV][8] */) {
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 64);
-  }
+__device__ __forceinline__ void across_waves(double (&v)[NV], double* sh /* [NV][8] */) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) {
 #pragma unroll
@@ -581,6 +593,14 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* sh /* [NV][8]
       v[i] = s;
     }
   }
+}
+
+// Block sum of NV doubles held one set per thread; thread 0 gets the result.
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* sh /* [NV][8] */) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
+  across_waves<NV>(v, sh);
 }
 
 // FP64 partial sums of (rho, j_x, j_y, j_z), j = sum fbar e + F/2, per block.
@@ -805,22 +825,30 @@ __device__ __forceinline__ uint64_t per_item(uint64_t n) {
 // of them, one segment per wavefront.  The other form's sums over a thread's
 // nodes are multiply-adds in the arithmetic's precision, in their order: here the
 // wavefronts leave the factors in LDS and the block goes through them in that
-// order afterwards, for the same sums.  (FP64 leaves the products; the sums may
-// differ in the last bit.)  Adjoint step with its reduction, 64^3 D3Q27 FP32: 61.4
-// -> 28.2 us (the reduction in one launch instead of two is 9.7 of that), 32^3 60.6
-// -> 13.6, 96 x 50 x 50 with walls 94.3 -> 42.2, 64^3 D3Q15 47.3 -> 16.8.
+// order afterwards, for the same sums.  (D3Q27's 46 factors in FP64 do not fit in
+// LDS: six pairs wait in registers and go there after the others have been added.
+// Leaving their products instead rounds once more per term, and is 3% faster.)
+// Adjoint step with its reduction, other form -> this, in us: D3Q27 FP32 64^3 55.2 -> 25.3
+// (the reduction in one launch instead of two is 9.7 of that), 32^3 58.8 -> 13.4,
+// 96 x 50 x 50 with walls 92 -> 43; D3Q15 FP32 64^3 43.2 -> 15.5; D3Q27 FP64 64^3 62 ->
+// 36.7, 32^3 62 -> 17.0.
 constexpr int kAdjSplitBlock = 512;
 template <int NB, typename R>
 struct Products {
-  R* p;   // FP32: the factors x, then, NB columns on, g; FP64: their products
+  static constexpr int late = sizeof(R) == 8 && NB == 23 ? 6 : 0;   // pairs 4 .. 3 + late wait in registers
+  static constexpr int columns = NB - late;
+  R* p;   // the factors x of pair b at column b - 4 - late and, `columns` on, g
+  R x[late ? late : 1], g[late ? late : 1];
 };
 template <int NB, typename R>
 __device__ __forceinline__ void add_product(Products<NB, R>& w, int b, R x, R g) {
-  if constexpr (sizeof(R) == 8) {
-    w.p[(b - 4) * kAdjSplitBlock] = x * g;
+  using P = Products<NB, R>;
+  if (b - 4 < P::late) {
+    w.x[b - 4] = x;
+    w.g[b - 4] = g;
   } else {
-    w.p[(b - 4) * kAdjSplitBlock] = x;
-    w.p[(NB + b - 4) * kAdjSplitBlock] = g;
+    w.p[(b - 4 - P::late) * kAdjSplitBlock] = x;
+    w.p[(P::columns + b - 4 - P::late) * kAdjSplitBlock] = g;
   }
 }
 template <int NB, typename R>
@@ -843,12 +871,13 @@ __global__ __launch_bounds__(SPLIT ? kAdjSplitBlock : kAdjBlock)
   // keep registers for the collision: dL/domega_b for b = 4..26; uF = dL/dF
   // for a uniform force.
   // (SPLIT: the factors and force gradients of each node)
-  __shared__ R wsh[SPLIT ? (sizeof(R) == 8 ? Q - 4 : 2 * (Q - 4)) * kAdjSplitBlock : 23 * kAdjBlock];
+  using Factors = Products<Q - 4, R>;
+  __shared__ R wsh[SPLIT ? 2 * Factors::columns * kAdjSplitBlock : 23 * kAdjBlock];
   __shared__ R fsh[SPLIT ? 3 * kAdjSplitBlock : 1];
-  std::conditional_t<SPLIT, Products<Q - 4, R>, LdsColumn<R>> wacc{wsh + threadIdx.x};
+  std::conditional_t<SPLIT, Factors, LdsColumn<R>> wacc{wsh + threadIdx.x};
   if constexpr (SPLIT) {
 #pragma unroll
-    for (int b = 0; b < (sizeof(R) == 8 ? Q - 4 : 2 * (Q - 4)); ++b) wsh[b * kAdjSplitBlock + threadIdx.x] = R(0);
+    for (int b = 0; b < 2 * Factors::columns; ++b) wsh[b * kAdjSplitBlock + threadIdx.x] = R(0);
 #pragma unroll
     for (int i = 0; i < 3; ++i) fsh[i * kAdjSplitBlock + threadIdx.x] = R(0);
   } else {
@@ -978,38 +1007,49 @@ __global__ __launch_bounds__(SPLIT ? kAdjSplitBlock : kAdjBlock)
     }
   }
   if constexpr (SPLIT) {
-    constexpr uint32_t B = kAdjSplitBlock, NB = Q - 4;
-    __syncthreads();
-    for (uint32_t c = wave; c < 26u; c += 8u) {
-      const uint32_t o = threadIdx.x & 63u;
+    constexpr uint32_t B = kAdjSplitBlock, NB = Q - 4, late = Factors::late, ncol = Factors::columns;
+    const uint32_t o = threadIdx.x & 63u;
+    auto chain = [&](uint32_t c) {          // the pairs at column c, in the order of the wavefronts
       R acc = R(0);
-      if (c < NB) {
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-          if constexpr (sizeof(R) == 8)
-            acc += wsh[c * B + k * 64u + o];
-          else
-            acc = fma_r(wsh[c * B + k * 64u + o], wsh[(NB + c) * B + k * 64u + o], acc);
-        }
-      } else if (c >= 23u) {
+      for (uint32_t k = 0; k < 8; ++k) acc = fma_r(wsh[c * B + k * 64u + o], wsh[(ncol + c) * B + k * 64u + o], acc);
+      return double(acc);
+    };
+    auto put = [&](uint32_t c, double s) {
+      if (o == 0) partials[uint64_t(blockIdx.x) * 26 + c] = s;
+    };
+    __syncthreads();
+    for (uint32_t c = late + wave; c < 26u; c += 8u) {
+      if (c < NB) {
+        put(c, wave_sum(chain(c - late)));
+      } else if (c < 23u) {
+        put(c, 0.0);
+      } else {
+        R acc = R(0);
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k) acc += fsh[(c - 23u) * B + k * 64u + o];
+        put(c, wave_sum(double(acc), double(args.force.scale)));
       }
-      double s = c < 23u ? double(acc) : double(acc) * double(args.force.scale);
+    }
+    if constexpr (late > 0) {
+      __syncthreads();
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-      if (o == 0) partials[uint64_t(blockIdx.x) * 26 + c] = s;
+      for (uint32_t b = 0; b < late; ++b) {
+        wsh[b * B + threadIdx.x] = wacc.x[b];
+        wsh[(ncol + b) * B + threadIdx.x] = wacc.g[b];
+      }
+      __syncthreads();
+      if (wave < late) put(wave, wave_sum(chain(wave)));
     }
   } else {
     double v[26];
 #pragma unroll
-    for (int b = 4; b < 27; ++b) v[b - 4] = b < Q ? double(wacc[b]) : 0.0;
+    for (int b = 4; b < 27; ++b) v[b - 4] = b < Q ? wave_sum(double(wacc[b])) : 0.0;
     __syncthreads();
-    v[23] = double(uF[0]) * double(args.force.scale);
-    v[24] = double(uF[1]) * double(args.force.scale);
-    v[25] = double(uF[2]) * double(args.force.scale);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[23 + i] = wave_sum(double(uF[i]), double(args.force.scale));
     __shared__ double sh[26 * 8];
-    block_sum<26>(v, sh);
+    across_waves<26>(v, sh);
     if (threadIdx.x == 0) {
 #pragma unroll
       for (int i = 0; i < 26; ++i) partials[uint64_t(blockIdx.x) * 26 + i] = v[i];

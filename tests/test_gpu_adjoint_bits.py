@@ -52,8 +52,7 @@ def _adjoint(q, prec, per_mass, f, lam, solid, force, rates, scale=1.0):
 
 
 @WALLS
-@pytest.mark.parametrize("q,prec,per_mass", [(27, F32, False), (27, F32, True), (15, F32, True), (15, F32, False),
-                                             (27, F16DEV, False), (15, BF16DEV, True)])
+@KINDS
 def test_sums_of_both_forms(q, prec, per_mass, walls):
     rows = (144, 128) if q == 15 and prec != F64 else (72, 64)
     one, two = adjoint_launch(q, prec, rows + (64,)), adjoint_launch(q, prec, rows + (128,))
