@@ -12,7 +12,9 @@ which takes two steps in one pass over the lattice where that pays), the HBM
 roofline of the single-step kernel, launched K times more after the timed window
 (algorithmic 228 B per node update: 27 FP32 loads + 27 FP32 stores + 3 FP32 force
 loads), the FP64 CPU oracle timed on a bounded sample, the
-adjoint/forward time ratio of a 100-step checkpointed adjoint, and the
+adjoint/forward time ratio of a 100-step checkpointed adjoint (the backward sweep
+over as many forward steps: `adjoint_forward_ratio` over single-step launches, which
+the gradient's own forward pass takes, `adjoint_run_ratio` over the timed run), and the
 per-launch step time of every lattice/storage variant on the same workload,
 two-buffer and in-place, of the FP32 adjoint step of both lattices, and
 (`walls`) of the step (two-buffer and in place), the adjoint step and the
@@ -378,6 +380,14 @@ def wall_sweep(n, launches=6):
     return out
 
 
+def adjoint_ratios(adjoint, kernel_ms, run_ms):
+    """The backward sweep's time over that of as many forward steps, as single-step
+    launches of kernel_ms (how benchmark_adjoint_ratio reports it) and at run_ms a step
+    of the timed run."""
+    single = adjoint["ratio_backward_over_forward_steps"]
+    return {"adjoint_forward_ratio": single, "adjoint_run_ratio": round(single * kernel_ms / run_ms, 3)}
+
+
 def _launch_ms(launch, count, per_launch=False):
     """Duration of each of `count` launches (event pair around each on the
     launch stream); their mean, or the list with per_launch."""
@@ -496,7 +506,9 @@ def main():
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None if traffic is None else round(traffic / (kernel_ms * 1e-3) / 1e9, 1),
                      "algorithmic_bytes_per_node": BYTES_PER_NODE, "kernel": "k_step<27,StF32,false>",
-                     "kernel_ms_avg": round(kernel_ms, 4)},
+                     "kernel_ms_avg": round(kernel_ms, 4),
+                     "of": "single-step launches after the timed run, which takes two steps in one pass (k_step2) "
+                           "but for its last one to four"},
         "mass_total_fp64": tot[0],
         "nonfinite_populations": nonfinite,
         "check_finite_ms": round(check_ms, 3),
@@ -517,10 +529,9 @@ def main():
     if not args.no_adjoint:
         from paper_1202_6081_amd import autograd as ag
         result["adjoint"] = ag.benchmark_adjoint_ratio(sim, args.adjoint_steps, forward_ms_per_step=kernel_ms)
-        result["adjoint_forward_ratio"] = result["adjoint"]["ratio_backward_over_forward_steps"]
+        result.update(adjoint_ratios(result["adjoint"], kernel_ms, ms_per_step))
     else:
-        result["adjoint"] = None
-        result["adjoint_forward_ratio"] = None
+        result.update({"adjoint": None, "adjoint_forward_ratio": None, "adjoint_run_ratio": None})
     torch.cuda.empty_cache()
     result["variants"] = None if args.no_variants else variant_sweep(n)
     result["adjoint_variants"] = None if args.no_variants else adjoint_sweep(n)
