@@ -19,10 +19,7 @@
 //     inverse transform.
 #pragma once
 
-#include <type_traits>
-#include <utility>
-
-#include "collide_d3q27.hpp"   // Rates<R>
+#include "collide_d3q27.hpp"   // Rates<R>, unroll
 #include "lattice.hpp"
 
 namespace cmlbm {
@@ -58,7 +55,7 @@ CMLBM_HDC int k15_norm(int b) {
 
 // Compile-time tables: kB15.v[b][a] = K_b(e_a), kM15.v[m][a] = the monomial m
 // (order below) at e_a, kD15[b] = D_b.  Loops over them run through
-// static_for so that every entry is a literal constant in the generated code.
+// unroll so that every entry is a literal constant in the generated code.
 struct Tab15 {
   int v[15][15];
 };
@@ -89,20 +86,6 @@ CMLBM_HDC Tab15 make_mono15() {
 constexpr Tab15 kB15 = make_basis15();
 constexpr Tab15 kM15 = make_mono15();
 
-template <int I>
-using Ic = std::integral_constant<int, I>;
-
-template <class Fn, int... I>
-CMLBM_HD void static_for_impl(Fn&& fn, std::integer_sequence<int, I...>) {
-  (fn(Ic<I>{}), ...);
-}
-
-// fn(Ic<0>{}), ..., fn(Ic<N-1>{}): the index is a compile-time constant.
-template <int N, class Fn>
-CMLBM_HD void static_for(Fn&& fn) {
-  static_for_impl(fn, std::make_integer_sequence<int, N>{});
-}
-
 // Source S_a = sum_b K_b(e_a) m^s_b / D_b with the printed m^s (Appendix G).
 template <typename R>
 CMLBM_HD void source15(R Fx, R Fy, R Fz, R ux, R uy, R uz, R (&S)[15]) {
@@ -124,13 +107,13 @@ CMLBM_HD void source15(R Fx, R Fy, R Fz, R ux, R uy, R uz, R (&S)[15]) {
   ms[13] = Fx * uy * uz + Fy * ux * uz + Fz * ux * uy;
   ms[14] = R(20) * (Fx * ux * (R(3) * (uy2 + uz2) - R(4)) + Fy * uy * (R(3) * (ux2 + uz2) - R(4)) +
                     Fz * uz * (R(3) * (ux2 + uy2) - R(4)));
-  static_for<15>([&](auto b) {
+  unroll<15>([&](auto b) {
     constexpr int d = k15_norm(decltype(b)::value);
     ms[b] *= R(1.0 / d);
   });
-  static_for<15>([&](auto a) {
+  unroll<15>([&](auto a) {
     R acc = R(0);
-    static_for<14>([&](auto b1) {
+    unroll<14>([&](auto b1) {
       constexpr int k = kB15.v[decltype(b1)::value + 1][decltype(a)::value];
       if constexpr (k != 0) acc += R(k) * ms[decltype(b1)::value + 1];
     });
@@ -169,13 +152,13 @@ template <int AX, typename R>
 CMLBM_HD void shift15(R (&m)[15], R u, R sg) {
   constexpr Groups15 G = groups15<AX>();
   const R v = sg * u;
-  static_for<G.nt>([&](auto i) {
+  unroll<G.nt>([&](auto i) {
     constexpr int a = G.t[decltype(i)::value][0], b = G.t[decltype(i)::value][1], c = G.t[decltype(i)::value][2];
     const R nb = m[b] + v * m[a];           // m2 + 2 v m1 + v^2 m0 = m2 + v (m1 + nb)
     m[c] = m[c] + v * (m[b] + nb);
     m[b] = nb;
   });
-  static_for<G.np>([&](auto i) {
+  unroll<G.np>([&](auto i) {
     constexpr int a = G.p[decltype(i)::value][0], b = G.p[decltype(i)::value][1];
     m[b] += v * m[a];
   });
@@ -285,40 +268,60 @@ CMLBM_HD void moments0_15(const R (&f)[15], R Fx, R Fy, R Fz, R& rho, R& ux, R& 
 // 1, x, y, z, xy, xz, yz, xx, yy, zz, xyy, xxy, xxz, xyz, xxyy.  With K^T K = D
 // they follow from the printed projections m^s alone: e.g. the xx moment is
 // m^s_7/2 + m^s_8/6 + m^s_9/3 = 2 F_x u_x and the xyy moment is
-// (4/5) m^s_1 + m^s_10/10.
-// Added to the raw moments m.
+// (4/5) m^s_1 + m^s_10/10.  Here the sums of products that they and their adjoint share;
+// which of two products is fused is free where neither is needed elsewhere, and kept as
+// it is so that the gradients keep their bits.
 template <typename R>
-CMLBM_HD void add_source_raw15(R Fx, R Fy, R Fz, R ux, R uy, R uz, R (&m)[15]) {
+struct Source15 {
+  R ux2, uy2, uz2, Fu, Fv, Fw, Fxy, Fxz, Fyz, Fvw, Fuw, Fuv, cx, cy, cz, xy2, xz2, yz2;
+  CMLBM_HD Source15(R Fx, R Fy, R Fz, R ux, R uy, R uz) {
+    CMLBM_FMA_AS_WRITTEN
+    ux2 = ux * ux;
+    uy2 = uy * uy;
+    uz2 = uz * uz;
+    Fu = Fx * ux;
+    Fv = Fy * uy;
+    Fw = Fz * uz;
+    Fxy = fma_r(Fy, ux, Fx * uy);
+    Fxz = fma_r(Fx, uz, Fz * ux);
+    Fyz = fma_r(Fz, uy, Fy * uz);
+    Fvw = fma_r(Fz, uz, Fv);
+    Fuw = fma_r(Fz, uz, Fu);
+    Fuv = fma_r(Fy, uy, Fu);
+    xy2 = fma_r(uy, uy, ux2);
+    xz2 = fma_r(uz, uz, ux2);
+    yz2 = fma_r(uz, uz, uy2);
+    cx = fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1);
+    cy = fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1);
+    cz = fma_r(R(3), uz2, xy2) - R(1);
+  }
+};
+
+// Adds the raw moments of the source to m.
+template <typename R>
+CMLBM_HD void add_source_raw15(const Source15<R>& q, R Fx, R Fy, R Fz, R ux, R uy, R uz, R (&m)[15]) {
   CMLBM_FMA_AS_WRITTEN
-  const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
-  const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
-  const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
   m[MX] += Fx;
   m[MY] += Fy;
   m[MZ] += Fz;
-  m[MXY] += fma_r(Fx, uy, Fy * ux);
-  m[MXZ] += fma_r(Fx, uz, Fz * ux);
-  m[MYZ] += fma_r(Fz, uy, Fy * uz);
-  m[MXX] = fma_r(R(2), Fu, m[MXX]);
-  m[MYY] = fma_r(R(2), Fv, m[MYY]);
-  m[MZZ] = fma_r(R(2), Fw, m[MZZ]);
-  const R cx = fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1), cy = fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1);
-  const R cz = fma_r(R(3), uz2, xy2) - R(1);
-  m[MXYY] = fma_r(R(0.5), fma_r(ux + ux, fma_r(Fy, uy, Fw), Fx * cx), m[MXYY]);
-  m[MXXY] = fma_r(R(0.5), fma_r(uy + uy, fma_r(Fx, ux, Fw), Fy * cy), m[MXXY]);
-  m[MXXZ] = fma_r(R(0.5), fma_r(uz + uz, fma_r(Fy, uy, Fu), Fz * cz), m[MXXZ]);
-  m[MXYZ] += fma_r(uy, Fz * ux, fma_r(uz, Fx * uy, uz * (Fy * ux)));
-  m[MXXYY] = fma_r(R(2.0 / 3.0), fma_r(Fw, xy2, fma_r(Fu, yz2, Fv * xz2)), m[MXXYY]);
+  m[MXY] += q.Fxy;
+  m[MXZ] += q.Fxz;
+  m[MYZ] += q.Fyz;
+  m[MXX] = fma_r(R(2), q.Fu, m[MXX]);
+  m[MYY] = fma_r(R(2), q.Fv, m[MYY]);
+  m[MZZ] = fma_r(R(2), q.Fw, m[MZZ]);
+  m[MXYY] = fma_r(R(0.5), fma_r(Fx, q.cx, (ux + ux) * q.Fvw), m[MXYY]);
+  m[MXXY] = fma_r(R(0.5), fma_r(Fy, q.cy, (uy + uy) * q.Fuw), m[MXXY]);
+  m[MXXZ] = fma_r(R(0.5), fma_r(Fz, q.cz, (uz + uz) * q.Fuv), m[MXXZ]);
+  m[MXYZ] += fma_r(Fz * ux, uy, fma_r(Fx * uy, uz, Fy * ux * uz));
+  m[MXXYY] = fma_r(R(2.0 / 3.0), fma_r(q.Fw, q.xy2, fma_r(q.Fu, q.yz2, q.Fv * q.xz2)), m[MXXYY]);
 }
 
-// Adjoint of add_source_raw15 with respect to F and u (gr: adjoint of m).
+// Its adjoint with respect to F and u (gr: adjoint of m).
 template <typename R>
-CMLBM_HD void source_raw15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gr)[15], R& gFx, R& gFy, R& gFz,
-                               R& gux, R& guy, R& guz) {
+CMLBM_HD void source_raw15_adj(const Source15<R>& q, R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gr)[15], R& gFx,
+                               R& gFy, R& gFz, R& gux, R& guy, R& guz) {
   CMLBM_FMA_AS_WRITTEN
-  const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
-  const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
-  const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
   const R x2 = R(2) * ux, y2 = R(2) * uy, z2 = R(2) * uz;
   gFx += fma_r(x2, gr[7], fma_r(uz, gr[5], fma_r(uy, gr[4], gr[1])));
   gFy += fma_r(y2, gr[8], fma_r(uz, gr[6], fma_r(ux, gr[4], gr[2])));
@@ -327,46 +330,43 @@ CMLBM_HD void source_raw15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gr)
   guy += fma_r(R(2) * Fy, gr[8], fma_r(Fz, gr[6], Fx * gr[4]));
   guz += fma_r(R(2) * Fz, gr[9], fma_r(Fy, gr[6], Fx * gr[5]));
   // third order
-  const R cx = R(0.5) * (fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1));
-  const R cy = R(0.5) * (fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1));
-  const R cz = R(0.5) * (fma_r(R(3), uz2, xy2) - R(1));
+  const R hx = R(0.5) * q.cx, hy = R(0.5) * q.cy, hz = R(0.5) * q.cz;
   const R uxy = ux * uy, uxz = ux * uz, uyz = uy * uz;
-  gFx += fma_r(uxz, gr[12], fma_r(cx, gr[10], uxy * gr[11]));
-  gFy += fma_r(uyz, gr[12], fma_r(uxy, gr[10], cy * gr[11]));
-  gFz += fma_r(cz, gr[12], fma_r(uxz, gr[10], uyz * gr[11]));
-  const R Fvw = Fv + Fw, Fuw = Fu + Fw, Fuv = Fu + Fv;
-  const R Fxy = fma_r(Fx, uy, Fy * ux), Fxz = fma_r(Fx, uz, Fz * ux), Fyz = fma_r(Fy, uz, Fz * uy);
-  gux += fma_r(Fxz, gr[12], fma_r(fma_r(R(3), Fu, Fvw), gr[10], Fxy * gr[11]));
-  guy += fma_r(Fyz, gr[12], fma_r(Fxy, gr[10], fma_r(R(3), Fv, Fuw) * gr[11]));
-  guz += fma_r(fma_r(R(3), Fw, Fuv), gr[12], fma_r(Fxz, gr[10], Fyz * gr[11]));
+  gFx += fma_r(uxz, gr[12], fma_r(hx, gr[10], uxy * gr[11]));
+  gFy += fma_r(uyz, gr[12], fma_r(uxy, gr[10], hy * gr[11]));
+  gFz += fma_r(hz, gr[12], fma_r(uxz, gr[10], uyz * gr[11]));
+  gux += fma_r(q.Fxz, gr[12], fma_r(fma_r(Fz, uz, fma_r(R(3), q.Fu, q.Fv)), gr[10], q.Fxy * gr[11]));
+  guy += fma_r(q.Fyz, gr[12], fma_r(q.Fxy, gr[10], fma_r(Fz, uz, fma_r(R(3), q.Fv, q.Fu)) * gr[11]));
+  guz += fma_r(fma_r(Fy, uy, fma_r(R(3), q.Fw, q.Fu)), gr[12], fma_r(q.Fxz, gr[10], q.Fyz * gr[11]));
   gFx = fma_r(uyz, gr[13], gFx);
   gFy = fma_r(uxz, gr[13], gFy);
   gFz = fma_r(uxy, gr[13], gFz);
-  gux = fma_r(Fyz, gr[13], gux);
-  guy = fma_r(Fxz, gr[13], guy);
-  guz = fma_r(Fxy, gr[13], guz);
+  gux = fma_r(q.Fyz, gr[13], gux);
+  guy = fma_r(q.Fxz, gr[13], guy);
+  guz = fma_r(q.Fxy, gr[13], guz);
   // fourth order
   const R c = R(2.0 / 3.0) * gr[14];
-  gFx = fma_r(c * ux, yz2, gFx);
-  gFy = fma_r(c * uy, xz2, gFy);
-  gFz = fma_r(c * uz, xy2, gFz);
-  gux = fma_r(c, fma_r(Fx, yz2, x2 * Fvw), gux);
-  guy = fma_r(c, fma_r(Fy, xz2, y2 * Fuw), guy);
-  guz = fma_r(c, fma_r(Fz, xy2, z2 * Fuv), guz);
+  gFx = fma_r(c * ux, q.yz2, gFx);
+  gFy = fma_r(c * uy, q.xz2, gFy);
+  gFz = fma_r(c * uz, q.xy2, gFz);
+  gux = fma_r(c, fma_r(Fx, q.yz2, x2 * q.Fvw), gux);
+  guy = fma_r(c, fma_r(Fy, q.xz2, y2 * q.Fuw), guy);
+  guz = fma_r(c, fma_r(Fz, q.xy2, z2 * q.Fuv), guz);
 }
 
-// shift15 with its multiply-adds as written.
-template <int AX, typename R>
-CMLBM_HD void shift15_as_written(R (&m)[15], R v) {
+// shift15 with its multiply-adds as written.  GIVEN: the first triple's first moment,
+// shifted, is first.
+template <int AX, bool GIVEN = false, typename R>
+CMLBM_HD void shift15_as_written(R (&m)[15], R v, R first = R(0)) {
   constexpr Groups15 G = groups15<AX>();
-  static_for<G.nt>([&](auto i) {
+  unroll<G.nt>([&](auto i) {
     CMLBM_FMA_AS_WRITTEN
     constexpr int a = G.t[decltype(i)::value][0], b = G.t[decltype(i)::value][1], c = G.t[decltype(i)::value][2];
-    const R nb = fma_r(v, m[a], m[b]);
+    const R nb = GIVEN && a == 0 ? first : fma_r(v, m[a], m[b]);
     m[c] = fma_r(v, m[b] + nb, m[c]);
     m[b] = nb;
   });
-  static_for<G.np>([&](auto i) {
+  unroll<G.np>([&](auto i) {
     CMLBM_FMA_AS_WRITTEN
     constexpr int a = G.p[decltype(i)::value][0], b = G.p[decltype(i)::value][1];
     m[b] = fma_r(v, m[a], m[b]);
@@ -384,8 +384,29 @@ CMLBM_HD void collide15(R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& p) {
   const R ux = fma_r(R(0.5), Fx, m[MX]) * inv_rho;
   const R uy = fma_r(R(0.5), Fy, m[MY]) * inv_rho;
   const R uz = fma_r(R(0.5), Fz, m[MZ]) * inv_rho;
-  // raw moments of h = f + S, then central moments about u
-  add_source_raw15(Fx, Fy, Fz, ux, uy, uz, m);
+  // raw moments of h = f + S (the source's as in add_source_raw15), then central moments
+  // about u
+  {
+    const R ux2 = ux * ux, uy2 = uy * uy, uz2 = uz * uz;
+    const R Fu = Fx * ux, Fv = Fy * uy, Fw = Fz * uz;
+    const R xy2 = fma_r(uy, uy, ux2), xz2 = fma_r(ux, ux, uz2), yz2 = fma_r(uy, uy, uz2);
+    m[MX] += Fx;
+    m[MY] += Fy;
+    m[MZ] += Fz;
+    m[MXY] += fma_r(Fx, uy, Fy * ux);
+    m[MXZ] += fma_r(Fx, uz, Fz * ux);
+    m[MYZ] += fma_r(Fz, uy, Fy * uz);
+    m[MXX] = fma_r(R(2), Fu, m[MXX]);
+    m[MYY] = fma_r(R(2), Fv, m[MYY]);
+    m[MZZ] = fma_r(R(2), Fw, m[MZZ]);
+    const R cx = fma_r(uz, uz, fma_r(R(3), ux2, uy2)) - R(1), cy = fma_r(uz, uz, fma_r(R(3), uy2, ux2)) - R(1);
+    const R cz = fma_r(R(3), uz2, xy2) - R(1);
+    m[MXYY] = fma_r(R(0.5), fma_r(ux + ux, fma_r(Fy, uy, Fw), Fx * cx), m[MXYY]);
+    m[MXXY] = fma_r(R(0.5), fma_r(uy + uy, fma_r(Fx, ux, Fw), Fy * cy), m[MXXY]);
+    m[MXXZ] = fma_r(R(0.5), fma_r(uz + uz, fma_r(Fy, uy, Fu), Fz * cz), m[MXXZ]);
+    m[MXYZ] += fma_r(uy, Fz * ux, fma_r(uz, Fx * uy, uz * (Fy * ux)));
+    m[MXXYY] = fma_r(R(2.0 / 3.0), fma_r(Fw, xy2, fma_r(Fu, yz2, Fv * xz2)), m[MXXYY]);
+  }
   shift15_as_written<0>(m, -ux);
   shift15_as_written<1>(m, -uy);
   shift15_as_written<2>(m, -uz);
@@ -451,22 +472,30 @@ CMLBM_HD void initial15(R rho, R ux, R uy, R uz, R Fx, R Fy, R Fz, R (&f)[15]) {
 // shifts as in the forward collision).
 // ---------------------------------------------------------------------------
 // Adjoint of shift15: m = its input, g = adjoint of its output (in place ->
-// adjoint of its input); adds d/du to gu.
-template <int AX, typename R>
-CMLBM_HD void shift15_adj(const R (&m)[15], R u, R sg, R (&g)[15], R& gu) {
+// adjoint of its input); adds d/du to gu.  GU, GA: bit i for the second of the two products
+// of triple i's sum for gu, and of that for its first moment, being the fused one (free,
+// as above).  GIVEN, first: as in shift15_as_written.
+template <int AX, unsigned GU, unsigned GA, bool GIVEN = false, typename R>
+CMLBM_HD void shift15_adj(const R (&m)[15], R u, R sg, R (&g)[15], R& gu, R first = R(0)) {
   CMLBM_FMA_AS_WRITTEN
   constexpr Groups15 G = groups15<AX>();
-  const R v = sg * u;
+  const R v = sg * u, vv = v * v;
   R gv = R(0);
-  static_for<G.nt>([&](auto i) {
+  unroll<G.nt>([&](auto i) {
     CMLBM_FMA_AS_WRITTEN
-    constexpr int a = G.t[decltype(i)::value][0], b = G.t[decltype(i)::value][1], c = G.t[decltype(i)::value][2];
-    const R g1 = g[b], g2 = g[c];
-    gv += fma_r(g1, m[a], R(2) * g2 * fma_r(v, m[a], m[b]));
-    g[a] += fma_r(v, g1, v * v * g2);
+    constexpr int I = decltype(i)::value, a = G.t[I][0], b = G.t[I][1], c = G.t[I][2];
+    const R g1 = g[b], g2 = g[c], nb = GIVEN && a == 0 ? first : fma_r(v, m[a], m[b]), gg = R(2) * g2;
+    if constexpr (GU >> I & 1)
+      gv += fma_r(gg, nb, g1 * m[a]);
+    else
+      gv += fma_r(g1, m[a], gg * nb);
+    if constexpr (GA >> I & 1)
+      g[a] += fma_r(vv, g2, v * g1);
+    else
+      g[a] += fma_r(v, g1, vv * g2);
     g[b] = fma_r(R(2) * v, g2, g1);
   });
-  static_for<G.np>([&](auto i) {
+  unroll<G.np>([&](auto i) {
     CMLBM_FMA_AS_WRITTEN
     constexpr int a = G.p[decltype(i)::value][0], b = G.p[decltype(i)::value][1];
     gv = fma_r(g[b], m[a], gv);
@@ -478,9 +507,9 @@ CMLBM_HD void shift15_adj(const R (&m)[15], R u, R sg, R (&g)[15], R& gu) {
 // Raw moments of h, and the transpose (adjoint) of that linear map.
 template <typename R>
 CMLBM_HD void raw15(const R (&h)[15], R (&r)[15]) {
-  static_for<15>([&](auto m) {
+  unroll<15>([&](auto m) {
     R acc = R(0);
-    static_for<15>([&](auto a) {
+    unroll<15>([&](auto a) {
       constexpr int k = kM15.v[decltype(m)::value][decltype(a)::value];
       if constexpr (k == 1) acc += h[a];
       if constexpr (k == -1) acc -= h[a];
@@ -489,14 +518,21 @@ CMLBM_HD void raw15(const R (&h)[15], R (&r)[15]) {
   });
 }
 
+// gr[12 .. 14] = w[m] x[m - 12], fused into the sums.
 template <typename R>
-CMLBM_HD void raw15_adj(const R (&gr)[15], R (&gh)[15]) {
-  static_for<15>([&](auto a) {
+CMLBM_HD void raw15_adj(const R (&gr)[15], const R (&w)[27], const R (&x)[3], R (&gh)[15]) {
+  unroll<15>([&](auto a) {
+    CMLBM_FMA_AS_WRITTEN
     R acc = R(0);
-    static_for<15>([&](auto m) {
-      constexpr int k = kM15.v[decltype(m)::value][decltype(a)::value];
-      if constexpr (k == 1) acc += gr[m];
-      if constexpr (k == -1) acc -= gr[m];
+    unroll<15>([&](auto m) {
+      CMLBM_FMA_AS_WRITTEN
+      constexpr int M = decltype(m)::value, k = kM15.v[M][decltype(a)::value];
+      if constexpr (M >= 12 && k != 0)
+        acc = fma_r(k == 1 ? w[M] : -w[M], x[M - 12], acc);
+      else if constexpr (k == 1)
+        acc += gr[M];
+      else if constexpr (k == -1)
+        acc -= gr[M];
     });
     gh[a] = acc;
   });
@@ -545,10 +581,10 @@ template <typename R>
 CMLBM_HD void source15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gS)[15], R& gFx, R& gFy, R& gFz,
                            R& gux, R& guy, R& guz) {
   R G[15];
-  static_for<14>([&](auto b1) {
+  unroll<14>([&](auto b1) {
     constexpr int b = decltype(b1)::value + 1;
     R acc = R(0);
-    static_for<15>([&](auto a) {
+    unroll<15>([&](auto a) {
       constexpr int k = kB15.v[b][decltype(a)::value];
       if constexpr (k != 0) acc += R(k) * gS[a];
     });
@@ -602,21 +638,31 @@ CMLBM_HD void source15_adj(R Fx, R Fy, R Fz, R ux, R uy, R uz, const R (&gS)[15]
 
 // Adjoint of collide15.  f: pre-collision populations.  g: on entry the
 // adjoint of the post-collision populations, on exit the adjoint of f.  Adds
-// the force adjoint and gw[b] (adjoint of omega_b, b = 4..14).
-template <int PM = -1, typename R, typename W>
+// the force adjoint and gw[b] (adjoint of omega_b, b = 4..14).  PM: attractor form,
+// 0 literal, 1 per unit mass, -1 as p.per_mass says (run time).  STORED16: populations
+// are stored in 16 bits; the shifted z moment is F_z/2 + rho u_z with F_z/2 fused instead of
+// rho u_z (free, as above).
+template <int PM = -1, bool STORED16 = false, typename R, typename W>
 CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& p, R (&g)[15], R& gFx, R& gFy,
                             R& gFz, W& gw) {
   CMLBM_FMA_AS_WRITTEN
-  const bool pm = PM < 0 ? p.per_mass != 0 : PM != 0;
+  if constexpr (PM < 0) {
+    if (p.per_mass)
+      collide15_adj<1, STORED16>(f, Fx, Fy, Fz, p, g, gFx, gFy, gFz, gw);
+    else
+      collide15_adj<0, STORED16>(f, Fx, Fy, Fz, p, g, gFx, gFy, gFz, gw);
+    return;
+  }
   R rho, ux, uy, uz, inv_rho;
   moments0_15(f, Fx, Fy, Fz, rho, ux, uy, uz, inv_rho);
   R gux = R(0), guy = R(0), guz = R(0), grho = R(0);
-  const R sm = pm ? inv_rho : R(1);
+  const R sm = PM > 0 ? inv_rho : R(1);
 
   // forward: central moments c of h = f + S (raw moments of f plus those of S)
   R c[15];
   raw15(f, c);
-  add_source_raw15(Fx, Fy, Fz, ux, uy, uz, c);
+  const Source15<R> q(Fx, Fy, Fz, ux, uy, uz);
+  add_source_raw15(q, Fx, Fy, Fz, ux, uy, uz, c);
   shift15_as_written<0>(c, -ux);
   shift15_as_written<1>(c, -uy);
   shift15_as_written<2>(c, -uz);
@@ -625,8 +671,8 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
   const R d1 = p.wc[7] * D1;
   const R t9 = fma_r(p.w[9], rho, p.wc[9] * T);
   const R td = fma_r(p.wc[8], D2, t9 + t9);
-  const R txx = fma_r(d1, R(3), td) * R(1.0 / 6.0);
-  const R tyy = fma_r(d1, R(-3), td) * R(1.0 / 6.0);
+  const R txx = fma_r(R(3), d1, td) * R(1.0 / 6.0);
+  const R tyy = fma_r(R(-3), d1, td) * R(1.0 / 6.0);
   const R tzz = fma_r(-p.wc[8], D2, t9) * R(1.0 / 3.0);
   R t[15];
   t[0] = rho;
@@ -650,12 +696,27 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
     R v[15];   // input of the x shift = t shifted along z and y
 #pragma unroll
     for (int m = 0; m < 15; ++m) v[m] = t[m];
-    shift15_as_written<2>(v, uz);
-    shift15_as_written<1>(v, uy);
-    shift15_adj<0>(v, ux, R(1), gt, gux);
-    shift15_as_written<1>(v, -uy);   // undo: v = input of the y shift
-    shift15_adj<1>(v, uy, R(1), gt, guy);
-    shift15_adj<2>(t, uz, R(1), gt, guz);
+    const R z = STORED16 ? fma_r(R(0.5), Fz, uz * rho) : fma_r(uz, rho, t[3]);
+    shift15_as_written<2, true>(v, uz, z);
+    // along y (shift15), with the relaxed moments that are products fused into the sums
+    // that use them
+    {
+      const R n2 = fma_r(uy, v[0], v[2]), n4 = fma_r(uy, v[1], v[4]), n11 = fma_r(p.wc[11], c[11], uy * v[7]);
+      v[8] = fma_r(uy, v[2] + n2, v[8]);
+      v[10] = fma_r(uy, fma_r(p.wc[4], c[4], n4), v[10]);
+      v[14] = fma_r(uy, fma_r(p.wc[11], c[11], n11), v[14]);
+      v[2] = n2;
+      v[4] = n4;
+      v[11] = n11;
+      v[6] = fma_r(uy, v[3], v[6]);
+      v[13] = fma_r(uy, v[5], v[13]);
+    }
+    const R g6 = gt[6] + ux * gt[13];            // (both rounded)
+    shift15_adj<0, 0, 0>(v, ux, R(1), gt, gux);
+    gt[6] = g6;
+    shift15_as_written<1>(v, -uy);               // undo: v = input of the y shift
+    shift15_adj<1, 0, 0>(v, uy, R(1), gt, guy);
+    shift15_adj<2, 1, 1, true>(t, uz, R(1), gt, guz, z);
   }
   // relaxation
   grho += gt[0];
@@ -677,14 +738,19 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
   R gtxx = gt[7], gtyy = gt[8];
   const R gtzz = gt[9];
   {
-    const R G = gt[14];
-    const R txy = txx * tyy;
+    const R G = gt[14], gA = p.w[14] * G;
     gc[14] = p.wc[14] * G;
-    add_product(gw, 14, fma_r(txy, sm, -c[14]), G);
-    const R gA = p.w[14] * G;
-    if (pm) grho = fma_r(-sm * (txy * sm), gA, grho);
-    gtxx = fma_r(gA * tyy, sm, gtxx);
-    gtyy = fma_r(gA * txx, sm, gtyy);
+    if constexpr (PM > 0) {
+      const R txy = txx * tyy;
+      add_product(gw, 14, fma_r(txy, sm, -c[14]), G);
+      grho = fma_r(-sm * (txy * sm), gA, grho);
+      gtxx = fma_r(gA * tyy, sm, gtxx);
+      gtyy = fma_r(gA * txx, sm, gtyy);
+    } else {
+      add_product(gw, 14, fma_r(txx, tyy, -c[14]), G);
+      gtxx = fma_r(gA, tyy, gtxx);
+      gtyy = fma_r(gA, txx, gtyy);
+    }
   }
   {
     const R gxy = gtxx + gtyy, gzz3 = gtzz * R(1.0 / 3.0);
@@ -706,25 +772,33 @@ CMLBM_HD void collide15_adj(const R (&f)[15], R Fx, R Fy, R Fz, const Rates<R>& 
 #pragma unroll
     for (int m = 0; m < 15; ++m) v[m] = c[m];
     shift15_as_written<2>(v, uz);
-    shift15_adj<2>(v, uz, R(-1), gc, guz);
+    const R g4 = fma_r(p.wc[4], gt[4], -(uz * gc[13]));   // (gc4 = wc4 gt4 fused into its own update)
+    shift15_adj<2, 0, 0>(v, uz, R(-1), gc, guz);
+    gc[4] = g4;
     shift15_as_written<1>(v, uy);   // input of the y shift
-    shift15_adj<1>(v, uy, R(-1), gc, guy);
+    shift15_adj<1, 6, 7>(v, uy, R(-1), gc, guy);
     shift15_as_written<0>(v, ux);   // raw moments of h
-    shift15_adj<0>(v, ux, R(-1), gc, gux);
+    shift15_adj<0, 14, 15>(v, ux, R(-1), gc, gux);
   }
   // raw moments (of f and of the source), density and velocity
   R gh[15];
-  raw15_adj(gc, gh);
-  source_raw15_adj(Fx, Fy, Fz, ux, uy, uz, gc, gFx, gFy, gFz, gux, guy, guz);
+  const R unscaled[3] = {gt[12], gt[13], gt[14]};
+  raw15_adj(gc, p.wc, unscaled, gh);
+  source_raw15_adj(q, Fx, Fy, Fz, ux, uy, uz, gc, gFx, gFy, gFz, gux, guy, guz);
   const R inv = inv_rho;
   const R gjx = gux * inv, gjy = guy * inv, gjz = guz * inv;
   grho = fma_r(-fma_r(uz, guz, fma_r(uy, guy, ux * gux)), inv, grho);
   gFx = fma_r(R(0.5), gjx, gFx);
   gFy = fma_r(R(0.5), gjy, gFy);
   gFz = fma_r(R(0.5), gjz, gFz);
+  // (e = 0 adds 0 gj: a NaN or infinite gj reaches every population)
+  auto along = [&](int e, R gu, R gj, R acc) {
+    CMLBM_FMA_AS_WRITTEN
+    return e == 0 ? fma_r(R(0), gj, acc) : fma_r(e > 0 ? gu : -gu, inv, acc);
+  };
 #pragma unroll
   for (int a = 0; a < 15; ++a)
-    g[a] = fma_r(R(kE15[a].z), gjz, fma_r(R(kE15[a].y), gjy, fma_r(R(kE15[a].x), gjx, gh[a] + grho)));
+    g[a] = along(kE15[a].z, guz, gjz, along(kE15[a].y, guy, gjy, along(kE15[a].x, gux, gjx, gh[a] + grho)));
 }
 
 // Adjoint of the force dependence of initial15 (u0 fixed): fbar = f^eq - S/2.

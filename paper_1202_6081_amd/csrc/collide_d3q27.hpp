@@ -19,6 +19,9 @@
 // after them.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "lattice.hpp"
 
 namespace cmlbm {
@@ -44,6 +47,20 @@ struct Rates {
 // buffers, in place, two steps in one pass) or the adjoint (with running sums or with
 // their factors kept) would not agree bit for bit.
 #define CMLBM_FMA_AS_WRITTEN _Pragma("clang fp contract(off)")
+
+template <int I>
+using Ic = std::integral_constant<int, I>;
+
+template <class Fn, int... I>
+CMLBM_HD void unroll_impl(Fn&& fn, std::integer_sequence<int, I...>) {
+  (fn(Ic<I>{}), ...);
+}
+
+// fn(Ic<0>{}), ..., fn(Ic<N-1>{}): the index is a compile-time constant.
+template <int N, class Fn>
+CMLBM_HD void unroll(Fn&& fn) {
+  unroll_impl(fn, std::make_integer_sequence<int, N>{});
+}
 
 // -- 3-point transforms along one axis --------------------------------------
 // Populations (p_-, p_0, p_+) -> central moments (k0, k1, k2) about u:
@@ -94,16 +111,16 @@ CMLBM_HD void inv_line_as_written(R& a, R& b, R& c, R u) {
   c = HALVE ? R(0.5) * (r2 + r1) : r2 + r1;
 }
 
-// Adjoint of inv_line: (m0, m1) are the forward inputs, (ga, gb, gc) hold the
-// adjoints of the outputs on entry and of the inputs on exit; adds to gu.
+// Adjoint of inv_line: (m0, r1) are the forward input and the raw first moment, m1r1 =
+// m1 + r1, (ga, gb, gc) hold the adjoints of the outputs on entry and of the
+// inputs on exit; adds to gu.
 template <typename R>
-CMLBM_HD void inv_line_adj(R m0, R m1, R u, R& ga, R& gb, R& gc, R& gu) {
+CMLBM_HD void inv_line_adj(R m0, R m1r1, R u, R& ga, R& gb, R& gc, R& gu) {
   CMLBM_FMA_AS_WRITTEN
-  const R r1 = fma_r(u, m0, m1);
   const R pa = ga, pb = gb, pc = gc;
   const R gr2 = fma_r(R(0.5), pa + pc, -pb);
-  const R gr1 = fma_r(gr2, u, R(0.5) * (pc - pa));
-  gu = fma_r(gr2, m1 + r1, gu);
+  const R gr1 = fma_r(R(0.5), pc - pa, gr2 * u);
+  gu = fma_r(gr2, m1r1, gu);
   gu = fma_r(gr1, m0, gu);
   ga = fma_r(gr1, u, pb);
   gb = fma_r(gr2, u, gr1);
@@ -144,10 +161,12 @@ CMLBM_HD void unshift_line(R a, R& b, R& c, R u) {
 // Adjoint of shift_line from its output (k0, k1): (g0, g1, g2) hold the
 // adjoints of (k0, k1, k2) on entry and of (r0, r1, r2) on exit; with
 // k1 = r1 - u r0 and k2 = r2 - u (r1 + k1), dk2/du = -2 k1 and dk1/du = -k0.
-template <typename R>
+// SECOND: which of the two products is fused.
+template <bool SECOND, typename R>
 CMLBM_HD void shift_line_adj(R k0, R k1, R u, R& g0, R& g1, R g2, R& gu) {
   CMLBM_FMA_AS_WRITTEN
-  gu -= fma_r(k0, g1, R(2) * k1 * g2);
+  const R k2 = R(2) * k1;
+  gu -= SECOND ? fma_r(k2, g2, k0 * g1) : fma_r(k0, g1, k2 * g2);
   const R t = fma_r(-u, g2, g1);
   g0 = fma_r(-u, t, g0);
   g1 = fma_r(-u, g2, t);
@@ -214,15 +233,17 @@ CMLBM_HD void unshift_pass(R (&m)[27], R u) {
   }
 }
 
-// m: the output of shift_pass<AXIS> (central moments along AXIS).
+// m: the output of shift_pass<AXIS> (central moments along AXIS).  The sum for gu has
+// two products a line, neither of them needed elsewhere: which one is fused is free, and
+// fixed by the bits of SECOND (from the first line up) so that results keep their bits.
 template <int AXIS, typename R>
 CMLBM_HD void shift_pass_adj(const R (&m)[27], R u, R (&g)[27], R& gu) {
   constexpr int S = line_stride<AXIS>();
-#pragma unroll
-  for (int l = 0; l < 9; ++l) {
-    const int o = line_base<AXIS>(l);
-    shift_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], gu);
-  }
+  constexpr unsigned SECOND = AXIS == 2 ? 0xbe : AXIS == 1 ? 0x9e : 0xb0;
+  unroll<9>([&](auto l) {
+    constexpr int o = line_base<AXIS>(decltype(l)::value);
+    shift_line_adj<(SECOND >> decltype(l)::value & 1) != 0>(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], gu);
+  });
 }
 
 template <int AXIS, typename R>
@@ -255,21 +276,27 @@ CMLBM_HD void inv_pass_as_written(R (&m)[27], R u) {
   }
 }
 
+// m: the input of the inverse pass.
 template <int AXIS, typename R>
 CMLBM_HD void inv_pass_adj(const R (&m)[27], R u, R (&g)[27], R& gu) {
+  CMLBM_FMA_AS_WRITTEN
   constexpr int S = line_stride<AXIS>();
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
     const int o = line_base<AXIS>(l);
-    inv_line_adj(m[o], m[o + S], u, g[o], g[o + S], g[o + 2 * S], gu);
+    // (the z pass, lines with e_y = -1: with both roundings, as the raw first moment is
+    // a halved sum there)
+    const R m1 = m[o + S], r1 = AXIS == 2 && l % 3 == 0 ? m1 + u * m[o] : fma_r(u, m[o], m1);
+    inv_line_adj(m[o], m1 + r1, u, g[o], g[o + S], g[o + 2 * S], gu);
   }
 }
 
 // The diagonal second moments: their combinations D1 = xx - yy, D2 = xx + yy - 2 zz and
-// T = xx + yy + zz (g7, g8 relaxed toward 0, g9 toward rho) and the relaxed ones.
+// T = xx + yy + zz (g7, g8 relaxed toward 0, g9 toward rho), and the relaxed ones, kxx =
+// X/6, kyy = Y/6, kzz = Z/3.
 template <typename R>
 struct Diagonal27 {
-  R D1, D2, T, kxx, kyy, kzz;
+  R D1, D2, T, X, Y, Z, kxx, kyy, kzz;
   CMLBM_HD Diagonal27(R xx, R yy, R zz, R rho, const Rates<R>& p) {
     CMLBM_FMA_AS_WRITTEN
     const R xy2 = xx + yy;
@@ -277,84 +304,48 @@ struct Diagonal27 {
     D2 = fma_r(R(-2), zz, xy2);
     T = xy2 + zz;
     const R t = fma_r(p.w[9], rho, p.wc[9] * T);
-    const R d1 = p.wc[7] * D1, td = fma_r(R(2), t, p.wc[8] * D2);
-    kxx = fma_r(R(3), d1, td) * R(1.0 / 6.0);
-    kyy = fma_r(R(-3), d1, td) * R(1.0 / 6.0);
-    kzz = fma_r(-p.wc[8], D2, t) * R(1.0 / 3.0);
+    const R d1 = p.wc[7] * D1, td = fma_r(p.wc[8], D2, t + t);
+    X = fma_r(d1, R(3), td);
+    Y = fma_r(d1, R(-3), td);
+    Z = fma_r(-p.wc[8], D2, t);
+    kxx = X * R(1.0 / 6.0);
+    kyy = Y * R(1.0 / 6.0);
+    kzz = Z * R(1.0 / 3.0);
   }
 };
 
-// Relax the central moments in m (cube layout) in place.  PM: attractor form,
-// 0 literal, 1 per unit mass, -1 as p.per_mass says (run time).
-template <int PM = -1, typename R>
-CMLBM_HD void relax27(R (&m)[27], R rho, R inv_rho, R Fx, R Fy, R Fz, const Rates<R>& p) {
-  CMLBM_FMA_AS_WRITTEN
-  const bool pm = PM < 0 ? p.per_mass != 0 : PM != 0;
-  // conserved: density and first central moments F/2
-  m[K3(0, 0, 0)] = rho;
-  m[K3(1, 0, 0)] = R(0.5) * Fx;
-  m[K3(0, 1, 0)] = R(0.5) * Fy;
-  m[K3(0, 0, 1)] = R(0.5) * Fz;
-  // second order, off-diagonal (g4, g5, g6): attractor 0
-  m[K3(1, 1, 0)] *= p.wc[4];
-  m[K3(1, 0, 1)] *= p.wc[5];
-  m[K3(0, 1, 1)] *= p.wc[6];
-  // second order, diagonal
-  const Diagonal27<R> k(m[K3(2, 0, 0)], m[K3(0, 2, 0)], m[K3(0, 0, 2)], rho, p);
-  m[K3(2, 0, 0)] = k.kxx;
-  m[K3(0, 2, 0)] = k.kyy;
-  m[K3(0, 0, 2)] = k.kzz;
-  // third order: xyy+xzz (g10) with xyy-xzz (g13), and the y, z analogues
-  auto pair = [&](int i, int j, int bs, int bd) {
+// The attractors' sums and differences, axy = kxx kyy (over rho: per_mass) etc.: axy + axz
+// + ayz, axy + axz - 2 ayz and axy - axz.  PM: attractor form, 0 literal, 1 per unit mass.
+template <int PM, typename R>
+struct Attractors27 {
+  R axy, axz, ayz, a1, a2, a3;
+  CMLBM_HD Attractors27(const Diagonal27<R>& k, R sm) {
     CMLBM_FMA_AS_WRITTEN
-    const R s = m[i] + m[j], d = p.wc[bd] * (m[i] - m[j]);
-    m[i] = R(0.5) * fma_r(p.wc[bs], s, d);
-    m[j] = R(0.5) * fma_r(p.wc[bs], s, -d);
-  };
-  pair(K3(1, 2, 0), K3(1, 0, 2), 10, 13);
-  pair(K3(2, 1, 0), K3(0, 1, 2), 11, 14);
-  pair(K3(2, 0, 1), K3(0, 2, 1), 12, 15);
-  m[K3(1, 1, 1)] *= p.wc[16];
-  // fourth order, diagonal pairs (g17, g18, g19) toward the factorized attractors
-  const R sm = pm ? inv_rho : R(1);
-  const R kys = k.kyy * sm, kzs = k.kzz * sm;
-  {
-    const R axz = k.kxx * kzs, ayz = k.kyy * kzs, axy_xz = fma_r(k.kxx, kys, axz);
-    const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
-    const R q1 = fma_r(p.wc[17], A + B + C, p.w[17] * (axy_xz + ayz));
-    const R q2 = fma_r(p.wc[18], fma_r(R(-2), C, A + B), p.w[18] * fma_r(R(-2), ayz, axy_xz));
-    const R q3 = fma_r(p.wc[19], A - B, p.w[19] * fma_r(k.kxx, kys, -axz));
-    const R ab = fma_r(R(2), q1, q2);
-    m[K3(0, 2, 2)] = (q1 - q2) * R(1.0 / 3.0);
-    m[K3(2, 2, 0)] = R(0.5) * fma_r(ab, R(1.0 / 3.0), q3);
-    m[K3(2, 0, 2)] = R(0.5) * fma_r(ab, R(1.0 / 3.0), -q3);
+    const R xy = k.kxx * k.kyy, xz = k.kxx * k.kzz, yz = k.kyy * k.kzz;
+    R xy_xz;
+    if constexpr (PM) {
+      axy = xy * sm;
+      axz = xz * sm;
+      ayz = yz * sm;
+      xy_xz = fma_r(xy, sm, axz);
+      a1 = fma_r(yz, sm, xy_xz);
+      a3 = fma_r(xy, sm, -axz);
+    } else {
+      axy = xy;
+      axz = xz;
+      ayz = yz;
+      xy_xz = fma_r(k.kxx, k.kzz, xy);
+      a1 = fma_r(k.kyy, k.kzz, xy_xz);
+      a3 = fma_r(-k.kxx, k.kzz, xy);
+    }
+    a2 = fma_r(R(-2), ayz, xy_xz);
   }
-  m[K3(2, 1, 1)] *= p.wc[20];
-  m[K3(1, 2, 1)] *= p.wc[21];
-  m[K3(1, 1, 2)] *= p.wc[22];
-  // fifth order
-  m[K3(1, 2, 2)] *= p.wc[23];
-  m[K3(2, 1, 2)] *= p.wc[24];
-  m[K3(2, 2, 1)] *= p.wc[25];
-  // sixth order toward kxx kyy kzz (g26)
-  m[K3(2, 2, 2)] = fma_r(p.wc[26], m[K3(2, 2, 2)], p.w[26] * (k.kxx * kys * kzs));
-}
+};
 
-// The relaxation of relax27 and the inverse pass along x (inv_pass<0, false>) in
-// one, from central moments to populations along x.  A relaxed moment that is a
-// product is fused into the sums that use it where it can be.
+// Third order pairs relaxed, xyy + xzz (g10) with xyy - xzz (g13) and the y, z
+// analogues: twice the moments.
 template <typename R>
-CMLBM_HD void relax_unshift_x27(R (&m)[27], R rho, R inv_rho, R ux, R Fx, R Fy, R Fz, const Rates<R>& p) {
-  CMLBM_FMA_AS_WRITTEN
-  constexpr R third = R(1.0 / 3.0), sixth = R(1.0 / 6.0), half = R(0.5);
-  // second order, diagonal: kxx = sixth X, kyy = sixth Y, kzz = third Z
-  const R xx = m[K3(2, 0, 0)], yy = m[K3(0, 2, 0)], zz = m[K3(0, 0, 2)];
-  const R D1 = xx - yy, xy2 = yy + xx, D2 = fma_r(R(-2), zz, xy2);
-  const R t = fma_r(p.w[9], rho, p.wc[9] * (zz + xy2));
-  const R d1 = p.wc[7] * D1, td = fma_r(p.wc[8], D2, t + t);
-  const R X = fma_r(d1, R(3), td), Y = fma_r(d1, R(-3), td), Z = fma_r(-p.wc[8], D2, t);
-  const R kxx = X * sixth, kyy = Y * sixth, kzz = Z * third;
-  // third order pairs (twice the moments)
+CMLBM_HD void relax_pairs27(R (&m)[27], const Rates<R>& p) {
   auto pair = [&](int i, int j, int bs, int bd) {
     CMLBM_FMA_AS_WRITTEN
     const R s = m[i] + m[j], d = p.wc[bd] * (m[i] - m[j]);
@@ -364,24 +355,23 @@ CMLBM_HD void relax_unshift_x27(R (&m)[27], R rho, R inv_rho, R ux, R Fx, R Fy, 
   pair(K3(1, 2, 0), K3(1, 0, 2), 10, 13);
   pair(K3(2, 1, 0), K3(0, 1, 2), 11, 14);
   pair(K3(2, 0, 1), K3(0, 2, 1), 12, 15);
-  // fourth order, diagonal: m022 = third T
-  const R sm = p.per_mass ? inv_rho : R(1);
-  const R kxy = kxx * kyy, kyz = kzz * kyy;
-  const R axz = sm * (kzz * kxx), ayz = sm * kyz;
-  const R axy_xz = fma_r(sm, kxy, axz);
-  const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
-  const R q1 = fma_r(p.wc[17], C + (A + B), p.w[17] * fma_r(sm, kyz, axy_xz));
-  const R q2 = fma_r(p.wc[18], fma_r(R(-2), C, A + B), p.w[18] * fma_r(R(-2), ayz, axy_xz));
-  const R q3 = fma_r(p.wc[19], A - B, p.w[19] * fma_r(sm, kxy, -axz));
-  const R ab = fma_r(R(2), q1, q2), T = q1 - q2;
-  const R m220 = half * fma_r(ab, third, q3), m202 = half * fma_r(ab, third, -q3), m022 = third * T;
-  // sixth order
-  const R m222 = fma_r(p.wc[26], m[K3(2, 2, 2)], p.w[26] * ((sm * sm) * (kzz * kxy)));
+}
+
+// The inverse pass along x from relaxed moments, of which m still holds the unrelaxed
+// ones that are only multiplied by a factor, and twice the third order pairs: the factors
+// are fused into the sums that use the moments.  k: the diagonal second order, m220 and
+// m202 of the fourth, and its m022 = T/3; m222.  HALVE as in inv_line.
+template <bool HALVE, typename R>
+CMLBM_HD void unshift_x27(R (&m)[27], R rho, R ux, R Fx, R Fy, R Fz, const Rates<R>& p, R kxx, R kyy, R kzz, R Y, R Z,
+                          R m220, R m202, R T, R m222) {
+  CMLBM_FMA_AS_WRITTEN
+  constexpr R third = R(1.0 / 3.0), sixth = R(1.0 / 6.0), half = R(0.5);
   // the lines along x: (raw first moment, raw second, rest) -> (p_-, p_0, p_+)
   auto line = [&](int o, R r1, R r2, R rest) {
-    m[o] = r2 - r1;
+    CMLBM_FMA_AS_WRITTEN
+    m[o] = HALVE ? half * (r2 - r1) : r2 - r1;
     m[o + 9] = rest;
-    m[o + 18] = r2 + r1;
+    m[o + 18] = HALVE ? half * (r2 + r1) : r2 + r1;
   };
   {
     const R r1 = fma_r(half, Fx, rho * ux), r2 = fma_r(ux, fma_r(half, Fx, r1), kxx);
@@ -416,9 +406,32 @@ CMLBM_HD void relax_unshift_x27(R (&m)[27], R rho, R inv_rho, R ux, R Fx, R Fy, 
   odd(K3(0, 1, 2), p.wc[22], m[K3(1, 1, 2)], p.wc[24], m[K3(2, 1, 2)]);
   {
     const R m122 = m[K3(1, 2, 2)];
-    const R r1 = fma_r(p.wc[23], m122, ux * m022), r2 = fma_r(ux, fma_r(p.wc[23], m122, r1), m222);
+    const R r1 = fma_r(p.wc[23], m122, ux * (third * T)), r2 = fma_r(ux, fma_r(p.wc[23], m122, r1), m222);
     line(K3(0, 2, 2), r1, r2, fma_r(T, third, -r2));
   }
+}
+
+// Relaxation and the inverse pass along x in one, from central moments to populations
+// along x (not halved).
+template <typename R>
+CMLBM_HD void relax_unshift_x27(R (&m)[27], R rho, R inv_rho, R ux, R Fx, R Fy, R Fz, const Rates<R>& p) {
+  CMLBM_FMA_AS_WRITTEN
+  constexpr R third = R(1.0 / 3.0), half = R(0.5);
+  const Diagonal27<R> k(m[K3(2, 0, 0)], m[K3(0, 2, 0)], m[K3(0, 0, 2)], rho, p);
+  relax_pairs27(m, p);
+  // fourth order, diagonal: m022 = third T
+  const R sm = p.per_mass ? inv_rho : R(1);
+  const R kxy = k.kxx * k.kyy, kyz = k.kzz * k.kyy;
+  const R axz = sm * (k.kzz * k.kxx), ayz = sm * kyz;
+  const R axy_xz = fma_r(sm, kxy, axz);
+  const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
+  const R q1 = fma_r(p.wc[17], C + (A + B), p.w[17] * fma_r(sm, kyz, axy_xz));
+  const R q2 = fma_r(p.wc[18], fma_r(R(-2), C, A + B), p.w[18] * fma_r(R(-2), ayz, axy_xz));
+  const R q3 = fma_r(p.wc[19], A - B, p.w[19] * fma_r(sm, kxy, -axz));
+  const R ab = fma_r(R(2), q1, q2);
+  const R m222 = fma_r(p.wc[26], m[K3(2, 2, 2)], p.w[26] * ((sm * sm) * (k.kzz * kxy)));
+  unshift_x27<false>(m, rho, ux, Fx, Fy, Fz, p, k.kxx, k.kyy, k.kzz, k.Y, k.Z, half * fma_r(ab, third, q3),
+                     half * fma_r(ab, third, -q3), q1 - q2, m222);
 }
 
 // Full collision: cube-ordered pre-collision populations in, post-collision out.
@@ -461,29 +474,78 @@ CMLBM_HD void sub_product(W& gw, int b, R x, R g) {
   add_product(gw, b, -x, g);
 }
 
-// Adjoint of relax27.  m: pre-relaxation central moments (unchanged).  g: on
+// The same for the adjoint's replay, with the attractor form compiled in, and the pass
+// along y as well: m holds the input of the z inverse pass on exit.
+template <int PM, typename R>
+CMLBM_HD void relax_unshift_xy27(R (&m)[27], R rho, R inv_rho, R ux, R uy, R Fx, R Fy, R Fz, const Rates<R>& p) {
+  CMLBM_FMA_AS_WRITTEN
+  constexpr R third = R(1.0 / 3.0), half = R(0.5);
+  const Diagonal27<R> k(m[K3(2, 0, 0)], m[K3(0, 2, 0)], m[K3(0, 0, 2)], rho, p);
+  relax_pairs27(m, p);
+  const R sm = PM ? inv_rho : R(1);
+  const Attractors27<PM, R> a(k, sm);
+  const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
+  const R q1 = fma_r(p.wc[17], A + B + C, p.w[17] * a.a1);
+  const R q2 = fma_r(p.wc[18], fma_r(R(-2), C, A + B), p.w[18] * a.a2);
+  const R q3 = fma_r(p.wc[19], A - B, p.w[19] * a.a3);
+  const R ab = fma_r(R(2), q1, q2);
+  const R m222 = fma_r(p.wc[26], m[K3(2, 2, 2)], p.w[26] * (k.kxx * k.kyy * k.kzz * (sm * sm)));
+  unshift_x27<false>(m, rho, ux, Fx, Fy, Fz, p, k.kxx, k.kyy, k.kzz, k.Y, k.Z, half * fma_r(ab, third, q3),
+                     half * fma_r(ab, third, -q3), q1 - q2, m222);
+  // the lines along y; those with e_x = +-1 come doubled
+#pragma unroll
+  for (int l = 0; l < 9; ++l) {
+    const int o = line_base<1>(l);
+    const R m0 = m[o], m1 = m[o + 3], m2 = m[o + 6];
+    R r1, r2;
+    if (l / 3 == 1) {
+      r1 = fma_r(uy, m0, m1);
+      r2 = fma_r(uy, m1 + r1, m2);
+      m[o + 3] = m0 - r2;
+    } else {
+      r1 = fma_r(half, m1, uy * (half * m0));
+      const R s = fma_r(half, m1, r1);
+      r2 = l % 3 == 2 ? fma_r(half, m2, uy * s) : fma_r(uy, s, half * m2);
+      m[o + 3] = fma_r(half, m0, -r2);
+    }
+    m[o] = half * (r2 - r1);
+    m[o + 6] = half * (r2 + r1);
+  }
+}
+
+// Two adjoints of relaxed moments before their factors: the sums that use wc4 x110 and
+// wc26 x222 fuse them.
+template <typename R>
+struct Unscaled27 {
+  R x110, x222;
+};
+
+// Adjoint of the relaxation.  m: pre-relaxation central moments (unchanged).  g: on
 // entry the adjoint of the relaxed moments, on exit the adjoint of m.  Adds to
 // grho, gF* and, through add_product, gw[b] (adjoint of omega_b, b = 4..26).
-template <int PM = -1, typename R, typename W>
-CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27], R& grho,
-                                            R& gFx, R& gFy, R& gFz, W& gw) {
+template <int PM, typename R, typename W>
+CMLBM_HD Unscaled27<R> relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27], R& grho, R& gFx, R& gFy,
+                                   R& gFz, W& gw) {
   CMLBM_FMA_AS_WRITTEN
-  const bool pm = PM < 0 ? p.per_mass != 0 : PM != 0;
   // recompute the second-order post values and attractor inputs
   const Diagonal27<R> k(m[K3(2, 0, 0)], m[K3(0, 2, 0)], m[K3(0, 0, 2)], rho, p);
   const R kxx = k.kxx, kyy = k.kyy, kzz = k.kzz;
   // per-mass attractors: A = P sm^(k-1), dA/drho = -(k-1) A sm
-  const R sm = pm ? R(1) / rho : R(1);
+  const R sm = PM ? R(1) / rho : R(1);
+  const Unscaled27<R> x{g[K3(1, 1, 0)], g[K3(2, 2, 2)]};
   R gkxx, gkyy, gkzz;
 
   // sixth order
   {
-    const R G = g[K3(2, 2, 2)];
-    const R s2 = sm * sm, kxy = kxx * kyy, kzs2 = kzz * s2;
-    add_product(gw, 26, fma_r(kxy, kzs2, -m[K3(2, 2, 2)]), G);
-    const R gP = p.w[26] * G;
-    if (pm) grho = fma_r(R(-2) * sm * (kxy * kzs2), gP, grho);
-    const R gPs = gP * s2;
+    const R G = x.x222;
+    const R s2 = sm * sm, kxy = kxx * kyy, gP = p.w[26] * G, gPs = gP * s2;
+    if constexpr (PM) {
+      const R kxyz = kxy * kzz;
+      add_product(gw, 26, fma_r(kxyz, s2, -m[K3(2, 2, 2)]), G);
+      grho = fma_r(R(-2) * sm * (kxyz * s2), gP, grho);
+    } else {
+      add_product(gw, 26, fma_r(kxy, kzz, -m[K3(2, 2, 2)]), G);
+    }
     gkxx = gPs * kyy * kzz;
     gkyy = gPs * kxx * kzz;
     gkzz = gPs * kxx * kyy;
@@ -503,20 +565,19 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
   scale(K3(1, 1, 2), 22);
   // fourth order diagonal
   {
-    const R kys = kyy * sm, kzs = kzz * sm;
-    const R axz = kxx * kzs, ayz = kyy * kzs, axy_xz = fma_r(kxx, kys, axz);
+    const Attractors27<PM, R> a(k, sm);
     const R A = m[K3(2, 2, 0)], B = m[K3(2, 0, 2)], C = m[K3(0, 2, 2)];
     const R gA = g[K3(2, 2, 0)], gB = g[K3(2, 0, 2)], gC = g[K3(0, 2, 2)];
     const R gAB = gA + gB;                                       // twice the adjoint of A + B
     const R gq3 = R(0.5) * (gA - gB);
     const R gq1 = (gC + gAB) * R(1.0 / 3.0);
     const R gq2 = fma_r(R(0.5), gAB, -gC) * R(1.0 / 3.0);
-    add_product(gw, 17, fma_r(kyy, kzs, axy_xz) - (A + B + C), gq1);
-    add_product(gw, 18, fma_r(R(-2), ayz, axy_xz) - fma_r(R(-2), C, A + B), gq2);
-    add_product(gw, 19, fma_r(kxx, kys, -axz) - (A - B), gq3);
+    add_product(gw, 17, a.a1 - (A + B + C), gq1);
+    add_product(gw, 18, a.a2 - fma_r(R(-2), C, A + B), gq2);
+    add_product(gw, 19, a.a3 - (A - B), gq3);
     const R ga1 = p.w[17] * gq1, ga2 = p.w[18] * gq2, ga12 = fma_r(p.w[18], gq2, ga1);
     const R gaxy = fma_r(p.w[19], gq3, ga12), gaxz = fma_r(-p.w[19], gq3, ga12), gayz = fma_r(R(-2), ga2, ga1);
-    if (pm) grho = fma_r(-sm, fma_r(ayz, gayz, fma_r(axz, gaxz, kxx * kys * gaxy)), grho);
+    if constexpr (PM) grho = fma_r(-sm, fma_r(a.ayz, gayz, fma_r(a.axy, gaxy, a.axz * gaxz)), grho);
     gkxx = fma_r(sm, fma_r(gaxy, kyy, gaxz * kzz), gkxx);
     gkyy = fma_r(sm, fma_r(gayz, kzz, gaxy * kxx), gkyy);
     gkzz = fma_r(sm, fma_r(gayz, kyy, gaxz * kxx), gkzz);
@@ -565,6 +626,7 @@ CMLBM_HD void relax27_adj(const R (&m)[27], R rho, const Rates<R>& p, R (&g)[27]
   gFy = fma_r(R(0.5), g[K3(0, 1, 0)], gFy);
   gFz = fma_r(R(0.5), g[K3(0, 0, 1)], gFz);
   g[K3(0, 0, 0)] = g[K3(1, 0, 0)] = g[K3(0, 1, 0)] = g[K3(0, 0, 1)] = R(0);
+  return x;
 }
 
 // Adjoint of collide27.  f: cube-ordered pre-collision populations on entry;
@@ -581,6 +643,13 @@ template <int PM = -1, typename R, typename W>
 CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (&g)[27], R (&s)[27],
                                               R& gFx, R& gFy, R& gFz, W& gw) {
   CMLBM_FMA_AS_WRITTEN
+  if constexpr (PM < 0) {                    // the attractor form as p says
+    if (p.per_mass)
+      collide27_adj<1>(f, Fx, Fy, Fz, p, g, s, gFx, gFy, gFz, gw);
+    else
+      collide27_adj<0>(f, Fx, Fy, Fz, p, g, s, gFx, gFy, gFz, gw);
+    return;
+  }
   R(&cm)[27] = f;
   raw_pass<2>(cm);
   raw_pass<1>(cm);
@@ -595,23 +664,25 @@ CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (
   shift_pass<2>(cm, uz);
   R gux = R(0), guy = R(0), guz = R(0), grho = R(0);
 
-  // relaxed moments, then replay the inverse passes to get each pass's input
+  // relax, then replay the inverse passes to get each pass's input
 #pragma unroll
   for (int k = 0; k < 27; ++k) s[k] = cm[k];
-  relax27<PM>(s, rho, inv_rho, Fx, Fy, Fz, p);
-  inv_pass_as_written<0>(s, ux);
-  inv_pass_as_written<1>(s, uy);             // s = input of the z inverse pass
+  relax_unshift_xy27<PM>(s, rho, inv_rho, ux, uy, Fx, Fy, Fz, p);   // s = input of the z inverse pass
   inv_pass_adj<2>(s, uz, g, guz);
   fwd_pass<1>(s, uy);                        // undo the y pass: s = input of the y inverse pass
   inv_pass_adj<1>(s, uy, g, guy);
   fwd_pass<0>(s, ux);                        // s = relaxed central moments
   inv_pass_adj<0>(s, ux, g, gux);
 
-  relax27_adj<PM>(cm, rho, p, g, grho, gFx, gFy, gFz, gw);
+  const Unscaled27<R> x = relax27_adj<PM>(cm, rho, p, g, grho, gFx, gFy, gFz, gw);
 
   // the shifts z, y, x in reverse; cm holds the output of the shift being
   // differentiated
-  shift_pass_adj<2>(cm, uz, g, guz);
+  {
+    const R t = fma_r(-uz, g[K3(1, 1, 2)], g[K3(1, 1, 1)]), g110 = fma_r(p.wc[4], x.x110, -(uz * t));
+    shift_pass_adj<2>(cm, uz, g, guz);
+    g[K3(1, 1, 0)] = g110;
+  }
   unshift_pass<2>(cm, uz);
   shift_pass_adj<1>(cm, uy, g, guy);
   unshift_pass<1>(cm, uy);
@@ -625,7 +696,12 @@ CMLBM_HD void collide27_adj(R (&f)[27], R Fx, R Fy, R Fz, const Rates<R>& p, R (
   gFx = fma_r(R(0.5), gux * inv_rho, gFx);
   gFy = fma_r(R(0.5), guy * inv_rho, gFy);
   gFz = fma_r(R(0.5), guz * inv_rho, gFz);
-  raw_pass_adj<0>(g);
+  {
+    const R t = fma_r(p.wc[26], x.x222, g[K3(0, 2, 2)]), g122 = g[K3(1, 2, 2)];
+    raw_pass_adj<0>(g);
+    g[K3(0, 2, 2)] = t - g122;
+    g[K3(2, 2, 2)] = t + g122;
+  }
   raw_pass_adj<1>(g);
   raw_pass_adj<2>(g);
 }

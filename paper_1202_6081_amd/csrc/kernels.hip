@@ -791,8 +791,8 @@ struct LdsColumn {
 // Waves per SIMD the adjoint is compiled for, at least and at most: three 27-vectors
 // and the line transforms fit 168 VGPRs in FP32 (3 waves); FP64 needs twice the
 // registers.  D3Q27 without walls would fit 128 in FP32, but a fourth wave is no gain: its
-// gathers evict what the others share (320 x 320 x 256 1740 against 1726 us, 128^3 165
-// against 157, 96^3 75 against 70; 200 x 90 x 80 131 against 134).
+// gathers evict what the others share (320 x 320 x 256 1736 against 1728 us, 128^3 163
+// against 158, 96^3 71 against 69; 200 x 90 x 80 129 against 134).
 #ifndef CMLBM_ADJ_WAVES_F32
 #define CMLBM_ADJ_WAVES_F32 3
 #endif
@@ -981,7 +981,7 @@ __global__ __launch_bounds__(SPLIT ? kAdjSplitBlock : kAdjBlock)
       R s[27];
       collide27_adj<PM>(f, Fx, Fy, Fz, args.rates, gm, s, gFx, gFy, gFz, wacc);
     } else {
-      collide15_adj<PM>(f, Fx, Fy, Fz, args.rates, gm, gFx, gFy, gFz, wacc);
+      collide15_adj<PM, sizeof(T) == 2>(f, Fx, Fy, Fz, args.rates, gm, gFx, gFy, gFz, wacc);
     }
     const uint64_t N = per_item(g.N);
 #pragma unroll

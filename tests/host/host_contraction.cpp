@@ -11,7 +11,7 @@ struct RateSum {
 };
 
 // out: the adjoint of f (Q), of the force (3) and of the rates (23, the first Q - 4 used)
-template <int Q, int PM, typename R>
+template <int Q, int PM, bool STORED16 = false, typename R>
 void adjoint(const R* f, const R* F, const double* omega, const R* g_in, R* out) {
   const cmlbm::Rates<R> p = rates<R>(Q, omega, PM);
   R gF[3] = {}, gw[27] = {}, m[Q], g[Q];
@@ -25,7 +25,7 @@ void adjoint(const R* f, const R* F, const double* omega, const R* g_in, R* out)
     R s[27];
     cmlbm::collide27_adj<PM>(m, F[0], F[1], F[2], p, g, s, gF[0], gF[1], gF[2], acc);
   } else {
-    cmlbm::collide15_adj<PM>(m, F[0], F[1], F[2], p, g, gF[0], gF[1], gF[2], acc);
+    cmlbm::collide15_adj<PM, STORED16>(m, F[0], F[1], F[2], p, g, gF[0], gF[1], gF[2], acc);
   }
   for (int a = 0; a < Q; ++a) out[a] = g[Q == 27 ? cmlbm::cube27(a) : a];
   for (int i = 0; i < 3; ++i) out[Q + i] = gF[i];
@@ -52,6 +52,15 @@ void hc_adjoint_bits_f64(int q, const double* f, const double* F, const double* 
 void hc_adjoint_bits_f32(int q, const float* f, const float* F, const double* omega, int per_mass, const float* g,
                          float* out) {
   adjoint<float>(q, f, F, omega, per_mass, g, out);
+}
+
+// (the arithmetic over 16-bit storage: D3Q15's differs in which product of a sum is fused)
+void hc_adjoint_bits_16(int q, const float* f, const float* F, const double* omega, int per_mass, const float* g,
+                        float* out) {
+  if (q == 27)
+    adjoint<float>(q, f, F, omega, per_mass, g, out);
+  else
+    per_mass ? adjoint<15, 1, true>(f, F, omega, g, out) : adjoint<15, 0, true>(f, F, omega, g, out);
 }
 
 }  // extern "C"
