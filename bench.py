@@ -507,8 +507,8 @@ def main():
                      "traffic": None if traffic is None else round(traffic / (kernel_ms * 1e-3) / 1e9, 1),
                      "algorithmic_bytes_per_node": BYTES_PER_NODE, "kernel": "k_step<27,StF32,false>",
                      "kernel_ms_avg": round(kernel_ms, 4),
-                     "of": "single-step launches after the timed run, which takes two steps in one pass (k_step2) "
-                           "but for its last one to four"},
+                     "of": "single-step launches after the timed run, which takes two steps in one pass where that pays "
+                           "(k_step2), but for its last one to four"},
         "mass_total_fp64": tot[0],
         "nonfinite_populations": nonfinite,
         "check_finite_ms": round(check_ms, 3),
