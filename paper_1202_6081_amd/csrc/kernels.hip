@@ -827,11 +827,11 @@ __device__ __forceinline__ uint64_t per_item(uint64_t n) {
 // wavefronts leave the factors in LDS and the block goes through them in that
 // order afterwards, for the same sums.  (D3Q27's 46 factors in FP64 do not fit in
 // LDS: six pairs wait in registers and go there after the others have been added.
-// Leaving their products instead rounds once more per term, and is 3% faster.)
-// Adjoint step with its reduction, other form -> this, in us: D3Q27 FP32 64^3 55.2 -> 25.3
-// (the reduction in one launch instead of two is 9.7 of that), 32^3 58.8 -> 13.4,
-// 96 x 50 x 50 with walls 92 -> 43; D3Q15 FP32 64^3 43.2 -> 15.5; D3Q27 FP64 64^3 62 ->
-// 36.7, 32^3 62 -> 17.0.
+// Leaving their products instead rounds once more per term; it is 2 to 10% faster.)
+// Adjoint step with its reduction, other form -> this, in us: D3Q27 FP32 64^3 55.0 -> 25.5
+// (the reduction in one launch instead of two is 9.7 of that), 32^3 58.7 -> 13.8,
+// 96 x 50 x 50 with walls 91 -> 43; D3Q15 FP32 64^3 43.6 -> 14.7; D3Q27 FP64 64^3 62.5 ->
+// 36.8, 32^3 62.4 -> 17.8.
 constexpr int kAdjSplitBlock = 512;
 template <int NB, typename R>
 struct Products {

@@ -179,9 +179,9 @@ inline int adjoint_block(const Geom& g) {
 
 // Whether the adjoint takes the form with a wavefront per row segment (k_adjoint's
 // SPLIT) on a lattice, and the rows of partial sums that its blocks leave.  The
-// factors of D3Q27 take 100 KB of LDS, one block on a CU: the form wins while
-// there are a few blocks per CU (640 blocks, 96 x 50 x 50: 35 against 63 us; 2304,
-// 96^3: 96 against 87), in FP64 likewise (43 against 74; 2048, 256 x 64 x 64: 201
+// factors of D3Q27 take 100 KB of LDS (148 in FP64), one block on a CU: the form wins while
+// there are a few blocks per CU (640 blocks, 96 x 50 x 50: 33 against 65 us; 2304,
+// 96^3: 96 against 87), in FP64 likewise (43 against 76; 2048, 256 x 64 x 64: 201
 // against 163).  D3Q15's take 51 KB in FP32 (2304 blocks: 46 against 57 us; 4096,
 // 128^3: 106 against 121).
 inline bool adjoint_split(int q, bool wide, const Geom& g) {
