@@ -186,8 +186,8 @@ cmlbm_status cmlbm_step_totals_noalloc(cmlbm_sim *sim, const void *f_in, void *f
 /* nsteps >= 0 steps ping-ponging between f_a and f_b, starting from f_a.
  * *result_in_b (may be NULL) is set to 1 when the last state is in f_b.  The
  * buffers hold the last two states, bit for bit those of nsteps calls of
- * cmlbm_step (large lattices take two steps in one pass over the populations
- * on the way there). */
+ * cmlbm_step (on the way there, lattices on which that is faster take two steps in
+ * one pass over the populations). */
 cmlbm_status cmlbm_run(cmlbm_sim *sim, void *f_a, void *f_b, int nsteps, void *stream, int *result_in_b);
 
 /* Copy a population buffer (blocked layout, storage type) into SoA
